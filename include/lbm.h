@@ -159,6 +159,9 @@ lbm_status lbm_bc(lbm_ctx* ctx);
  * moments (eq. (2)), gravity shift, equilibrium, f <- f + (f^eq - f)/tau. */
 lbm_status lbm_collide(lbm_ctx* ctx);
 /* n >= 0 times (propagate, bc, collide), split or fused per step_kind.
+ * Fused steps with LBM_X_WRAP run two to a pass over memory where n >= 4
+ * allows (in groups of four steps); the results are bitwise those of n single
+ * steps, for lbm_bc after it too.
  * It only launches kernels on the context's stream, so it can be captured
  * into a HIP graph there (after at least one eager step).  A replay repeats
  * the captured launches with the buffers they were captured with: capture an

@@ -14,6 +14,7 @@
 #include "lbm.h"
 #include "lbm_adjoint.hpp"
 #include "lbm_kernels.hpp"
+#include "lbm_twostep.hpp"
 
 using namespace lbm;
 
@@ -30,7 +31,7 @@ struct Plan {
     size_t wall_bytes;// one wall-density table (6 * lx doubles)
     size_t state_bytes; // snapshot: population buffer + its wall densities
     size_t off_buf[2];
-    size_t off_wall;  // 2 x 6 * lx doubles (double-buffered wall densities)
+    size_t off_wall;  // 3 x 6 * lx doubles (double-buffered wall densities, and those of the state in between)
     size_t off_part;  // RED_BLOCKS * 4 doubles, then 2 doubles of loss/dtau scratch
     size_t off_lam[2];
     size_t off_apart; // adjoint: one double per collide block
@@ -68,7 +69,7 @@ Plan plan(const lbm_params* p)
     size_t off = 0;
     pl.off_buf[0] = off; off += pl.buf_bytes;
     pl.off_buf[1] = off; off += pl.buf_bytes;
-    pl.off_wall = off; off += 2 * pl.wall_bytes;
+    pl.off_wall = off; off += 3 * pl.wall_bytes;
     pl.off_part = off; off += align_up(((size_t)RED_BLOCKS * 4 + 2) * 8, ALIGN);
     if (p->adjoint) {
         const size_t lb = align_up((size_t)pl.lgeo.total * (p->adjoint == 2 ? 4 : 8), ALIGN);
@@ -96,6 +97,7 @@ struct lbm_ctx {
     hipStream_t stream;
     int cur;           // current population buffer
     bool have_prev;    // the other buffer holds the state before the last propagate
+    bool prev_mid;     // ... except that the last pass took two steps: that state's wall densities are in table WALL_MID
     int lam_cur;
     bool have_lambda;
     // lambda buffer lam_cur holds mu of the last reverse step (lambda is its
@@ -113,10 +115,12 @@ struct lbm_ctx {
     unsigned collide_lds;// the same for the split step's collide
     bool dev_stores;     // fused and reverse steps with device-scope stores (dev_stores_for)
     unsigned adj_lds;    // the same for the reverse step
+    TwoStep two;         // how lbm_step takes two steps in one pass (fused step, wrapped index)
     std::string err;
 
     void* buf(int i) { return ws + pl.off_buf[i]; }
     double* wall_rho(int i) { return reinterpret_cast<double*>(ws + pl.off_wall + i * pl.wall_bytes); }
+    static constexpr int WALL_MID = 2;
     double* partials() { return reinterpret_cast<double*>(ws + pl.off_part); }
     double* scratch2() { return partials() + (size_t)RED_BLOCKS * 4; }
     template <typename L> L* lam(int i) { return reinterpret_cast<L*>(ws + pl.off_lam[i]); }
@@ -237,6 +241,7 @@ lbm_status do_propagate(lbm_ctx* c)
     if (c->wr_buf == 1 - c->cur) c->wr_buf = -1;   // destination overwritten
     c->cur = 1 - c->cur;
     c->have_prev = true;
+    c->prev_mid = false;
     return LBM_OK;
 }
 
@@ -246,10 +251,17 @@ lbm_status do_bc(lbm_ctx* c)
     if (c->p.ybc == LBM_Y_PERIODIC) return LBM_OK;
     if (!c->have_prev) return fail(c, LBM_ERR_STATE, "bc: no propagate since the state was set");
     const Geo& g = c->pl.geo;
-    lbm_status s = ensure_wall_density<S>(c, 1 - c->cur);
-    if (s) return s;
+    const double* wr = nullptr;
+    if (c->prev_mid) {
+        wr = c->wall_rho(lbm_ctx::WALL_MID);
+        c->wr_buf = -1;   // the current buffer's wall rows change
+    } else {
+        lbm_status s = ensure_wall_density<S>(c, 1 - c->cur);
+        if (s) return s;
+        wr = c->wall_rho(c->wr_cur);
+    }
     hipLaunchKernelGGL((k_bc_apply<S>), dim3((NSLOT * g.lx + 255) / 256), dim3(256), 0, c->stream,
-                       (S*)c->buf(c->cur), g, (const double*)c->wall_rho(c->wr_cur), c->wt);
+                       (S*)c->buf(c->cur), g, wr, c->wt);
     return check_launch(c, "bc_apply");
 }
 
@@ -349,6 +361,72 @@ lbm_status do_step_fused(lbm_ctx* c)
     if (s) return s;
     c->cur = 1 - c->cur;
     c->have_prev = true;
+    c->prev_mid = false;
+    if (walls) {
+        c->wr_cur = 1 - c->wr_cur;
+        c->wr_buf = c->cur;
+    }
+    return LBM_OK;
+}
+
+// Two fused steps in one pass, current buffer -> the other (lbm_twostep.hpp).
+template <typename S, bool WALLS, bool WIDE>
+void launch_two_step(lbm_ctx* c, const S* src, S* dst, const double* wr, double* mid, double* wo)
+{
+    const Geo& g = c->pl.geo;
+    auto tiles = [&](int tx, int ty) { return dim3((unsigned)(((g.lx + tx - 1) / tx) * ((g.ly + ty - 1) / ty))); };
+    switch (c->two.kind) {
+    case TWO_STEP_TILE_8X8:
+        hipLaunchKernelGGL((k_twostep_tile<S, WALLS, WIDE, 8, 8>), tiles(8, 8), dim3(tile_threads<8, 8>()), 0, c->stream,
+                           src, dst, g, c->cargs, wr, c->wt, mid, wo);
+        break;
+    case TWO_STEP_TILE_8X16:
+        hipLaunchKernelGGL((k_twostep_tile<S, WALLS, WIDE, 8, 16>), tiles(8, 16), dim3(tile_threads<8, 16>()), 0,
+                           c->stream, src, dst, g, c->cargs, wr, c->wt, mid, wo);
+        break;
+    case TWO_STEP_TILE_16X16:
+        hipLaunchKernelGGL((k_twostep_tile<S, WALLS, WIDE, 16, 16>), tiles(16, 16), dim3(tile_threads<16, 16>()), 0,
+                           c->stream, src, dst, g, c->cargs, wr, c->wt, mid, wo);
+        break;
+    default:
+        hipLaunchKernelGGL((k_twostep_march<S, WALLS, WIDE>), dim3((unsigned)c->two.march.nblk),
+                           dim3(2 * MarchShape<S>::waves * 64), 0, c->stream, src, dst, g, c->cargs, wr, c->wt, mid, wo,
+                           c->two.march);
+    }
+}
+
+template <typename S>
+lbm_status do_two_steps(lbm_ctx* c)
+{
+    S* src = (S*)c->buf(c->cur);
+    S* dst = (S*)c->buf(1 - c->cur);
+    lbm_status s = launch_pre_stream<S>(c, src);
+    if (s) return s;
+    const bool walls = c->p.ybc == LBM_Y_WALLS;
+    if (walls) {
+        s = ensure_wall_density<S>(c, c->cur);
+        if (s) return s;
+    }
+    const double* wr = c->wall_rho(c->wr_cur);
+    double* mid = c->wall_rho(lbm_ctx::WALL_MID);
+    double* wo = c->wall_rho(1 - c->wr_cur);
+    if constexpr (std::is_same<S, float>::value) {
+        if (c->f32_sums()) {
+            if (walls) launch_two_step<S, true, false>(c, src, dst, wr, mid, wo);
+            else launch_two_step<S, false, false>(c, src, dst, wr, mid, wo);
+        } else {
+            if (walls) launch_two_step<S, true, true>(c, src, dst, wr, mid, wo);
+            else launch_two_step<S, false, true>(c, src, dst, wr, mid, wo);
+        }
+    } else {
+        if (walls) launch_two_step<S, true, true>(c, src, dst, wr, mid, wo);
+        else launch_two_step<S, false, true>(c, src, dst, wr, mid, wo);
+    }
+    s = check_launch(c, "two_steps");
+    if (s) return s;
+    c->cur = 1 - c->cur;
+    c->have_prev = true;
+    c->prev_mid = walls;
     if (walls) {
         c->wr_cur = 1 - c->wr_cur;
         c->wr_buf = c->cur;
@@ -359,6 +437,16 @@ lbm_status do_step_fused(lbm_ctx* c)
 template <typename S>
 lbm_status do_step(lbm_ctx* c, int64_t n)
 {
+    // Passes of two steps go in pairs, so that every four steps end on the
+    // buffers they began with, as four single steps do (a graph of an even
+    // number of steps can then be replayed).
+    if (c->p.step_kind == LBM_STEP_FUSED && c->two.kind != TWO_STEP_NONE) {
+        for (; n >= 4; n -= 4) {
+            lbm_status s = do_two_steps<S>(c);
+            if (!s) s = do_two_steps<S>(c);
+            if (s) return s;
+        }
+    }
     for (int64_t i = 0; i < n; ++i) {
         lbm_status s;
         if (c->p.step_kind == LBM_STEP_FUSED) {
@@ -589,6 +677,7 @@ lbm_status lbm_create(const lbm_params* p, void* dev_workspace, size_t bytes, vo
     c->stream = (hipStream_t)hip_stream;
     c->cur = 0;
     c->have_prev = false;
+    c->prev_mid = false;
     c->lam_cur = 0;
     c->have_lambda = false;
     c->lam_is_mu = false;
@@ -606,6 +695,7 @@ lbm_status lbm_create(const lbm_params* p, void* dev_workspace, size_t bytes, vo
     c->fused_threads = SITE_THREADS;
     c->collide_lds = 0;
     c->dev_stores = false;
+    c->two = TwoStep{TWO_STEP_NONE, MarchLaunch{}};
     int dev = 0, ncu = 0, max_lds = 0;
     if (hipGetDevice(&dev) == hipSuccess &&
         hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess &&
@@ -614,6 +704,9 @@ lbm_status lbm_create(const lbm_params* p, void* dev_workspace, size_t bytes, vo
         c->fused_threads = fl.threads;
         c->fused_lds = fl.lds;
         c->dev_stores = dev_stores_for(site_grid(pl.geo).x, ncu);
+        if (p->step_kind == LBM_STEP_FUSED && p->xmode == LBM_X_WRAP)
+            c->two = p->precision == LBM_FP64 ? choose_two_step<double>(pl.geo, ncu, max_lds, p->ybc == LBM_Y_WALLS)
+                                              : choose_two_step<float>(pl.geo, ncu, max_lds, p->ybc == LBM_Y_WALLS);
         if ((size_t)site_grid(pl.geo).x >= (size_t)FUSED_FP64_CAP_MIN_BLOCKS_PER_CU * (size_t)ncu) {
             const unsigned coll = p->precision == LBM_FP64 ? COLLIDE_FP64_LDS_RESERVE : COLLIDE_FP32_LDS_RESERVE;
             if ((size_t)max_lds >= coll && (p->precision != LBM_FP64 || p->layout == LBM_LAYOUT_COLUMNS))

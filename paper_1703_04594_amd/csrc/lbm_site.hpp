@@ -92,13 +92,23 @@ template <> struct ShellK<float> {
     static constexpr F k5(int s) { return (F(C2) * F(SHELL_R2[s]) - F(6)) / F(4); }
 };
 
+// a b + c with one rounding.  The step's arithmetic names its fused products:
+// left to the compiler, which products of a sum are fused depends on the code
+// around them, and the kernels that inline a collision (fused, split, two
+// steps in a pass) would differ in the last bits.  Where both
+// terms of a sum are products, sum_of_products fuses the second.
+__device__ __forceinline__ double fma_(double a, double b, double c) { return __builtin_fma(a, b, c); }
+__device__ __forceinline__ float fma_(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
+template <typename C>
+__device__ __forceinline__ C sum_of_products(C a, C b, C c, C d) { return fma_(c, d, a * b); }
+
 // FP64 second moment sum_l |xi_l|^2 f_l with the per-population |xi_l|^2.
 template <typename V>
 __device__ __forceinline__ double xi2_moment(const V (&f)[NPOP])
 {
     double e = 0.0;
 #pragma unroll
-    for (int l = 1; l < NPOP; ++l) e += XI2.pop[l] * (double)f[l];
+    for (int l = 1; l < NPOP; ++l) e = fma_(XI2.pop[l], (double)f[l], e);
     return e;
 }
 
@@ -121,9 +131,9 @@ __device__ __forceinline__ void hop_moments(const C (&f)[NPOP], C& m0, C& sx, C&
 #pragma unroll
     for (int l = 0; l < NPOP; ++l) {
         m0 += f[l];
-        if (EX[l] != 0) sx += C(EX[l]) * f[l];
-        if (EY[l] != 0) sy += C(EY[l]) * f[l];
-        if (R2_OF(l) != 0) s2 += C(R2_OF(l)) * f[l];
+        if (EX[l] != 0) sx = fma_(C(EX[l]), f[l], sx);
+        if (EY[l] != 0) sy = fma_(C(EY[l]), f[l], sy);
+        if (R2_OF(l) != 0) s2 = fma_(C(R2_OF(l)), f[l], s2);
     }
 }
 
@@ -135,9 +145,9 @@ __device__ __forceinline__ void hop_moments_wide(const float (&f)[NPOP], double&
     for (int l = 0; l < NPOP; ++l) {
         const double v = (double)f[l];
         m0 += v;
-        if (EX[l] != 0) sx += (double)EX[l] * v;
-        if (EY[l] != 0) sy += (double)EY[l] * v;
-        if (R2_OF(l) != 0) s2 += (double)R2_OF(l) * v;
+        if (EX[l] != 0) sx = fma_((double)EX[l], v, sx);
+        if (EY[l] != 0) sy = fma_((double)EY[l], v, sy);
+        if (R2_OF(l) != 0) s2 = fma_((double)R2_OF(l), v, s2);
     }
 }
 
@@ -149,6 +159,20 @@ __host__ __device__ __forceinline__ C hop_dot(int l, C cux, C cuy)
     else if (EX[l] != 0) a = C(EX[l]) * cux;
     else if (EY[l] != 0) a = C(EY[l]) * cuy;
     return a;
+}
+
+// the same for (cux, cuy) = c (ux, uy), with one product of each sum fused
+// (products by 2 are exact)
+template <typename C>
+__device__ __forceinline__ C hop_fma(int l, C ux, C uy, C cux, C cuy)
+{
+#pragma clang fp contract(off)
+    const int ex = EX[l], ey = EY[l];
+    if (ex == 0 || ey == 0) return hop_dot<C>(l, cux, cuy);
+    if (ex == -1 && ey == -1) return fma_(-cscale<C>(), ux, -cuy);
+    if (ex * ex == 1 && ey * ey == 1) return fma_(C(ey) * cscale<C>(), uy, C(ex) * cux);
+    if (ex * ex > ey * ey) return fma_(C(ex), cux, C(ey) * cuy);
+    return fma_(C(ey), cuy, C(ex) * cux);
 }
 
 struct CollideArgs {
@@ -193,9 +217,16 @@ template <> __device__ __forceinline__ float arg_g<float>(const CollideArgs& a) 
 // WIDE = false (shifted form only) keeps every sum in FP32 as well: the
 // same collision with FP32 moment sums on both sides of the projection, for
 // measuring what the FP64 sums buy.
-template <typename C, bool SHIFTED, bool WIDE = true>
-__device__ __forceinline__ void collide_site(C (&f)[NPOP], const CollideArgs& args)
+//
+// mid() runs once the moments of f are taken, out(l) as soon as f[l] has its
+// final value.
+struct NoMid { __device__ __forceinline__ void operator()() const {} };
+struct NoOut { __device__ __forceinline__ void operator()(int) const {} };
+
+template <typename C, bool SHIFTED, bool WIDE = true, typename Mid = NoMid, typename Out = NoOut>
+__device__ __forceinline__ void collide_site(C (&f)[NPOP], const CollideArgs& args, Mid mid = Mid(), Out out = Out())
 {
+#pragma clang fp contract(off)
     using K = ShellK<C>;
     const C omega = arg_omega<C>(args);
     C m0, sx, sy, s2;
@@ -215,26 +246,27 @@ __device__ __forceinline__ void collide_site(C (&f)[NPOP], const CollideArgs& ar
     C th;
     if constexpr (SHIFTED) {
         // T - 1 = (sum (x2 - 2) d) / (2 rho) - u2 / 2
-        th = (c2scale<C>() * s2 - C(2) * m0) * inv * C(0.5) - (ux * ux + uy0 * uy0) * C(0.5);
+        th = fma_(c2scale<C>(), s2, C(-2) * m0) * inv * C(0.5) - sum_of_products(ux, ux, uy0, uy0) * C(0.5);
     } else {
         static_assert(sizeof(C) == 8, "the absolute form is FP64");
-        th = (xi2_moment(f) * inv - (ux * ux + uy0 * uy0)) * C(0.5) - C(1);
+        th = fma_(xi2_moment(f), inv, -sum_of_products(ux, ux, uy0, uy0)) * C(0.5) - C(1);
     }
-    const C uy = uy0 + arg_taug<C>(args);
+    mid();
+    const C uy = fma_(cscale<C>() * sy, inv, arg_taug<C>(args));   // uy0 + tau g
     th += arg_gth<C>(args);
-    const C u2 = ux * ux + uy * uy;
+    const C u2 = sum_of_products(ux, ux, uy, uy);
     const C cux = cscale<C>() * ux, cuy = cscale<C>() * uy;
     // shell-independent parts
     const C b1 = C(1) - C(0.5) * u2;             // A1 without th
     const C b2 = C(0.5) - C(0.25) * u2;          // A2 without th
-    const C b0m1 = u2 * (C(-0.5) + C(0.125) * u2); // A0 - 1 without th
+    const C b0m1 = u2 * fma_(C(0.125), u2, C(-0.5)); // A0 - 1 without th
     // populations are ordered by shell: form each shell's coefficients just
     // before its populations, so only one shell's worth is live
 #pragma unroll
     for (int s = 0; s < NSHELL; ++s) {
-        const C A0m1 = b0m1 + th * (K::k1(s) + u2 * K::k2(s) + th * K::k3(s));
-        const C A1 = b1 + th * K::k4(s);
-        const C A2 = b2 + th * K::k5(s);
+        const C A0m1 = fma_(th, fma_(th, K::k3(s), fma_(u2, K::k2(s), K::k1(s))), b0m1);
+        const C A1 = fma_(th, K::k4(s), b1);
+        const C A2 = fma_(th, K::k5(s), b2);
 #pragma unroll
         for (int l = 0; l < NPOP; ++l) {
             if (SHELL[l] != s) continue;
@@ -242,20 +274,21 @@ __device__ __forceinline__ void collide_site(C (&f)[NPOP], const CollideArgs& ar
             if (l == 0) {
                 pm = A0m1;
             } else {
-                const C a = hop_dot<C>(l, cux, cuy);
-                C t = a * C(1.0 / 24.0) + C(1.0 / 6.0);
-                t = t * a + A2;
-                t = t * a + A1;
-                pm = t * a + A0m1;
+                const C a = hop_fma<C>(l, ux, uy, cux, cuy);
+                C t = fma_(a, C(1.0 / 24.0), C(1.0 / 6.0));
+                t = fma_(t, a, A2);
+                t = fma_(t, a, A1);
+                pm = fma_(t, a, A0m1);
             }
-            C feq;
+            C df;   // f^eq - f
             if constexpr (SHIFTED) {
                 // d^eq = w ((rho - 1) P + (P - 1)) = w (m0 + rho (P - 1))
-                feq = wshell<C>(s) * (m0 + rho * pm);
+                df = fma_(wshell<C>(s), fma_(rho, pm, m0), -f[l]);
             } else {
-                feq = wshell<C>(s) * rho * (C(1) + pm);
+                df = fma_(wshell<C>(s) * rho, C(1) + pm, -f[l]);
             }
-            f[l] = f[l] + omega * (feq - f[l]);
+            f[l] = fma_(omega, df, f[l]);
+            if constexpr (!SHIFTED) out(l);
         }
     }
     if constexpr (SHIFTED) {
@@ -267,26 +300,29 @@ __device__ __forceinline__ void collide_site(C (&f)[NPOP], const CollideArgs& ar
             hop_moments_wide(f, M0, MX, MY, M2);
             d0 = (C)(m0d - M0);
             dx = (C)(sxd - MX);
-            dy = (C)(syd + (1.0 + m0d) * (args.g / cscale<double>()) - MY);
-            d2 = (C)(s2d + (double)(rho * (C(2) * g * uy0 + g * g) / c2) - M2);
+            dy = (C)(fma_(1.0 + m0d, args.g / cscale<double>(), syd) - MY);
+            d2 = (C)(s2d + (double)(rho * sum_of_products(C(2) * g, uy0, g, g) / c2) - M2);
         } else {
             C M0, MX, MY, M2;
             hop_moments<C>(f, M0, MX, MY, M2);
             d0 = m0 - M0;
             dx = sx - MX;
-            dy = sy + rho * (g / cscale<C>()) - MY;
-            d2 = s2 + rho * (C(2) * g * uy0 + g * g) / c2 - M2;
+            dy = fma_(rho, g / cscale<C>(), sy) - MY;
+            d2 = s2 + rho * sum_of_products(C(2) * g, uy0, g, g) / c2 - M2;
         }
         const C ka = C(2) * d0 - C(0.5) * c2 * d2;
         const C kb = c2 * dx, kc = c2 * dy;
-        const C kd = C(-0.5) * c2 * d0 + C(0.25) * c2 * c2 * d2;
+        const C kd = sum_of_products(C(-0.5) * c2, d0, C(0.25) * c2 * c2, d2);
 #pragma unroll
         for (int l = 0; l < NPOP; ++l) {
             C corr = ka;
-            if (EX[l] != 0) corr += C(EX[l]) * kb;
-            if (EY[l] != 0) corr += C(EY[l]) * kc;
-            if (R2_OF(l) != 0) corr += C(R2_OF(l)) * kd;
-            f[l] += wshell<C>(SHELL[l]) * corr;
+            if (EX[l] == 1 || EX[l] == -1) corr = fma_(C(EX[l]) * c2, dx, corr);
+            else if (EX[l] != 0) corr = fma_(C(EX[l]), kb, corr);
+            if (EY[l] == 1 || EY[l] == -1) corr = fma_(C(EY[l]) * c2, dy, corr);
+            else if (EY[l] != 0) corr = fma_(C(EY[l]), kc, corr);
+            if (R2_OF(l) != 0) corr = fma_(C(R2_OF(l)), kd, corr);
+            f[l] = fma_(wshell<C>(SHELL[l]), corr, f[l]);
+            out(l);
         }
     }
 }
