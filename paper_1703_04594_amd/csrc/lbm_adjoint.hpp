@@ -309,7 +309,7 @@ __global__ __launch_bounds__(SITE_THREADS) void k_adj_seed_T(const S* __restrict
     double loss = 0.0;
     if (y < g.ly) {
         double rho, ux, uy, T;
-        site_macros<S>(fbuf + g.origin + (long long)x * g.cs + y, g.ps, rho, ux, uy, T);
+        site_macros<S>(fbuf + g.origin + (long long)x * g.cs, (unsigned)y * (unsigned)sizeof(S), g.ps, rho, ux, uy, T);
         double d = d_in[(long long)x * g.ly + y];
         if (LOSS) { d = T - d; loss = 0.5 * d * d; }
         const double k = d / (2.0 * rho);

@@ -214,7 +214,8 @@ template <typename S>
 lbm_status launch_wall_density(lbm_ctx* c, const S* src, double* out)
 {
     const Geo& g = c->pl.geo;
-    hipLaunchKernelGGL((k_wall_density<S>), dim3((6 * g.lx + 255) / 256), dim3(256), 0, c->stream, src, g, out);
+    hipLaunchKernelGGL((k_wall_density<S>), dim3((6 * g.lx + WALL_DENSITY_THREADS - 1) / WALL_DENSITY_THREADS),
+                       dim3(WALL_DENSITY_THREADS), 0, c->stream, src, g, out);
     return check_launch(c, "wall_density");
 }
 
@@ -468,36 +469,59 @@ lbm_status do_step(lbm_ctx* c, int64_t n)
                  : ((c)->lam32() ? fn<float, float>(c, ##__VA_ARGS__) : fn<float, double>(c, ##__VA_ARGS__)))
 #define LAM_DISPATCH(c, fn, ...) ((c)->lam32() ? fn<float>(c, ##__VA_ARGS__) : fn<double>(c, ##__VA_ARGS__))
 
-template <typename S>
-lbm_status do_init(lbm_ctx* c, const double* rho, const double* ux, const double* uy, const double* T)
-{
-    hipLaunchKernelGGL((k_init_fields<S>), site_grid(c->pl.geo), dim3(SITE_THREADS), 0, c->stream,
-                       (S*)c->buf(c->cur), c->pl.geo, rho, ux, uy, T);
-    c->have_prev = false;
-    c->wr_buf = -1;
-    return check_launch(c, "init");
-}
-template <typename S>
-lbm_status do_init_rt(lbm_ctx* c, const double* P, RtProfile pr)
-{
-    hipLaunchKernelGGL((k_init_rt<S>), site_grid(c->pl.geo), dim3(SITE_THREADS), 0, c->stream,
-                       (S*)c->buf(c->cur), c->pl.geo, P, pr);
-    c->have_prev = false;
-    c->wr_buf = -1;
-    return check_launch(c, "init_rt");
-}
-template <typename S>
-lbm_status do_macros(lbm_ctx* c, double* rho, double* ux, double* uy, double* T)
-{
-    hipLaunchKernelGGL((k_macros<S>), site_grid(c->pl.geo), dim3(SITE_THREADS), 0, c->stream,
-                       (const S*)c->buf(c->cur), c->pl.geo, rho, ux, uy, T);
-    return check_launch(c, "macros");
-}
 // Copies take non-temporal accesses from this many bytes on: source and
 // destination then exceed the 256 MB Infinity Cache.  301 x 1030 FP64 (99 MB)
 // took 29 us without and 32 us with them, 1000 x 1501 FP32 (233 MB) 90 and 72.
 constexpr size_t COPY_NT_MIN_BYTES = 128u << 20;
 
+// Kernels that only read or only write a population buffer take non-temporal
+// accesses where the buffer alone exceeds the Infinity Cache (1000 x 1501 FP32,
+// 233 MB: init 35 us without and 45 with them, macros 37 and 55).
+constexpr size_t STREAM_NT_MIN_BYTES = 256u << 20;
+
+// the state was set, with its wall densities where there are walls
+void state_initialised(lbm_ctx* c)
+{
+    c->have_prev = false;
+    c->wr_buf = c->p.ybc == LBM_Y_WALLS ? c->cur : -1;
+}
+template <typename S>
+lbm_status do_init(lbm_ctx* c, const double* rho, const double* ux, const double* uy, const double* T)
+{
+    double* wr = c->p.ybc == LBM_Y_WALLS ? c->wall_rho(c->wr_cur) : nullptr;
+    if (c->pl.buf_bytes >= STREAM_NT_MIN_BYTES)
+        hipLaunchKernelGGL((k_init_fields<S, true>), site_grid(c->pl.geo), dim3(SITE_THREADS), 0, c->stream,
+                           (S*)c->buf(c->cur), c->pl.geo, rho, ux, uy, T, wr);
+    else
+        hipLaunchKernelGGL((k_init_fields<S, false>), site_grid(c->pl.geo), dim3(SITE_THREADS), 0, c->stream,
+                           (S*)c->buf(c->cur), c->pl.geo, rho, ux, uy, T, wr);
+    state_initialised(c);
+    return check_launch(c, "init");
+}
+template <typename S>
+lbm_status do_init_rt(lbm_ctx* c, const double* P, RtProfile pr)
+{
+    double* wr = c->p.ybc == LBM_Y_WALLS ? c->wall_rho(c->wr_cur) : nullptr;
+    if (c->pl.buf_bytes >= STREAM_NT_MIN_BYTES)
+        hipLaunchKernelGGL((k_init_rt<S, true>), site_grid(c->pl.geo), dim3(SITE_THREADS), 0, c->stream,
+                           (S*)c->buf(c->cur), c->pl.geo, P, pr, wr);
+    else
+        hipLaunchKernelGGL((k_init_rt<S, false>), site_grid(c->pl.geo), dim3(SITE_THREADS), 0, c->stream,
+                           (S*)c->buf(c->cur), c->pl.geo, P, pr, wr);
+    state_initialised(c);
+    return check_launch(c, "init_rt");
+}
+template <typename S>
+lbm_status do_macros(lbm_ctx* c, double* rho, double* ux, double* uy, double* T)
+{
+    if (c->pl.buf_bytes >= STREAM_NT_MIN_BYTES)
+        hipLaunchKernelGGL((k_macros<S, true>), site_grid(c->pl.geo), dim3(SITE_THREADS), 0, c->stream,
+                           (const S*)c->buf(c->cur), c->pl.geo, rho, ux, uy, T);
+    else
+        hipLaunchKernelGGL((k_macros<S, false>), site_grid(c->pl.geo), dim3(SITE_THREADS), 0, c->stream,
+                           (const S*)c->buf(c->cur), c->pl.geo, rho, ux, uy, T);
+    return check_launch(c, "macros");
+}
 template <typename S, bool TO_CANON, bool NT>
 void launch_canon(lbm_ctx* c, S* canon)
 {
@@ -584,10 +608,18 @@ lbm_status do_step_state(lbm_ctx* c, char* src, char* dst)
 }
 
 template <typename S>
+void launch_conservation_partial(const Geo& g, const S* buf, double* part, hipStream_t st)
+{
+    if (g.ly % 64 == 0 && (size_t)g.total * sizeof(S) >= STREAM_NT_MIN_BYTES)
+        hipLaunchKernelGGL((k_conservation_partial<S, true>), dim3(RED_BLOCKS), dim3(256), 0, st, buf, g, part);
+    else
+        hipLaunchKernelGGL((k_conservation_partial<S, false>), dim3(RED_BLOCKS), dim3(256), 0, st, buf, g, part);
+}
+
+template <typename S>
 lbm_status do_conservation(lbm_ctx* c, double* out4)
 {
-    hipLaunchKernelGGL((k_conservation_partial<S>), dim3(RED_BLOCKS), dim3(256), 0, c->stream,
-                       (const S*)c->buf(c->cur), c->pl.geo, c->partials());
+    launch_conservation_partial<S>(c->pl.geo, (const S*)c->buf(c->cur), c->partials(), c->stream);
     lbm_status s = check_launch(c, "conservation");
     if (s) return s;
     hipLaunchKernelGGL((k_reduce_partials<4, false>), dim3(1), dim3(REDUCE_THREADS), 0, c->stream,
@@ -653,7 +685,7 @@ Geo canonical_geo(int lx, int ly)
 template <typename S>
 lbm_status launch_conservation_noalloc(const Geo& g, const void* pops, double* part, double* out4, hipStream_t st)
 {
-    hipLaunchKernelGGL((k_conservation_partial<S>), dim3(RED_BLOCKS), dim3(256), 0, st, (const S*)pops, g, part);
+    launch_conservation_partial<S>(g, (const S*)pops, part, st);
     hipError_t e = hipGetLastError();
     if (e == hipSuccess) {
         hipLaunchKernelGGL((k_reduce_partials<4, false>), dim3(1), dim3(REDUCE_THREADS), 0, st,

@@ -315,20 +315,29 @@ __global__ __launch_bounds__(256) void k_fill_y_ghosts(S* __restrict__ buf, Geo 
 }
 
 // Density of the 3 rows next to each wall (FP64), for the wall rule.
-// wall_rho[(wall * 3 + k) * lx + x]: bottom row k, top row ly-1-k.
+// wall_rho[(wall * 3 + k) * lx + x]: bottom row k, top row ly-1-k.  A thread
+// per (column, wall row), the rows of a column side by side, in blocks of one
+// wave: the 37 loads of a thread are one chain of latency, so the waves are
+// spread over the CUs.
+constexpr int WALL_DENSITY_THREADS = 64;
 template <typename S>
-__global__ __launch_bounds__(256) void k_wall_density(const S* __restrict__ buf, Geo g, double* __restrict__ wall_rho)
+__global__ __launch_bounds__(WALL_DENSITY_THREADS) void k_wall_density(const S* __restrict__ buf, Geo g,
+                                                                       double* __restrict__ wall_rho)
 {
-    const int t = blockIdx.x * 256 + threadIdx.x;
+    const int t = blockIdx.x * WALL_DENSITY_THREADS + threadIdx.x;
     if (t >= 6 * g.lx) return;
-    const int x = t % g.lx, wk = t / g.lx;
+    const int x = t / 6, wk = t % 6;
     const int wall = wk / 3, k = wk % 3;
     const int y = wall == 0 ? k : g.ly - 1 - k;
     const S* p = buf + g.origin + (long long)x * g.cs + y;
+    S v[NPOP];
+#pragma unroll
+    for (int l = 0; l < NPOP; ++l) v[l] = p[(size_t)l * g.ps];
+    __builtin_amdgcn_sched_barrier(0);   // all loads before the first sum
     double r = 0.0;
 #pragma unroll
-    for (int l = 0; l < NPOP; ++l) r += (double)p[(size_t)l * g.ps];
-    wall_rho[t] = Store<S>::shifted ? 1.0 + r : r;
+    for (int l = 0; l < NPOP; ++l) r += (double)v[l];
+    wall_rho[wk * g.lx + x] = Store<S>::shifted ? 1.0 + r : r;
 }
 
 // Wall rule on the current buffer (split step): thread per (column, slot).
@@ -497,44 +506,58 @@ __global__ __launch_bounds__(T) void k_step_fused(const S* __restrict__ src, S* 
 // ---------------------------------------------------------------------------
 // Initial states, read-out, copies.
 // ---------------------------------------------------------------------------
-template <typename S>
+// A site's equilibrium of (rho, u, T), stored; its wall density (walls), summed
+// as k_wall_density sums it, into wall_rho unless that is NULL.  NT: streaming
+// stores, for large lattices (2048 x 4096 FP32 211 us against 255).
+template <typename S, bool NT>
+__device__ __forceinline__ void init_site(S* __restrict__ buf, const Geo& g, int x, int y, double rho, double ux, double uy,
+                                          double T, double* __restrict__ wall_rho)
+{
+    S* col = buf + g.origin + (long long)x * g.cs;
+    const unsigned yb = (unsigned)y * (unsigned)sizeof(S);
+    S f[NPOP];
+#pragma unroll
+    for (int l = 0; l < NPOP; ++l) {
+        f[l] = (S)feq_pop<Store<S>::shifted>(l, rho, ux, uy, T);
+        if constexpr (NT) st_nt(col + (size_t)l * g.ps, yb, f[l]);
+        else st_at(col + (size_t)l * g.ps, yb, f[l]);
+    }
+    if (wall_rho) store_wall_density<S>(f, g, x, y, wall_rho);
+}
+
+template <typename S, bool NT>
 __global__ __launch_bounds__(SITE_THREADS) void k_init_fields(S* __restrict__ buf, Geo g, const double* __restrict__ rho,
                                                            const double* __restrict__ ux, const double* __restrict__ uy,
-                                                           const double* __restrict__ T)
+                                                           const double* __restrict__ T, double* __restrict__ wall_rho)
 {
     const SiteBlock sb = site_block(g);
-    const int x = sb.x, y = sb.y;
-    if (y >= g.ly) return;
-    const long long s = (long long)x * g.ly + y;
-    const double r = rho[s], vx = ux[s], vy = uy[s], t = T[s];
-    S* p = buf + g.origin + (long long)x * g.cs + y;
-#pragma unroll
-    for (int l = 0; l < NPOP; ++l) p[(size_t)l * g.ps] = (S)feq_pop<Store<S>::shifted>(l, r, vx, vy, t);
+    if (sb.y >= g.ly) return;
+    const long long s = (long long)sb.x * g.ly + sb.y;
+    init_site<S, NT>(buf, g, sb.x, sb.y, rho[s], ux[s], uy[s], T[s], wall_rho);
 }
 
 struct RtProfile { double t_mid, t_amp, p0, width, y_mid; };
 
-template <typename S>
-__global__ __launch_bounds__(SITE_THREADS) void k_init_rt(S* __restrict__ buf, Geo g, const double* __restrict__ P, RtProfile pr)
+template <typename S, bool NT>
+__global__ __launch_bounds__(SITE_THREADS) void k_init_rt(S* __restrict__ buf, Geo g, const double* __restrict__ P, RtProfile pr,
+                                                       double* __restrict__ wall_rho)
 {
     const SiteBlock sb = site_block(g);
     const int x = sb.x, y = sb.y;
     if (y >= g.ly) return;
     const double T0 = pr.t_mid - pr.t_amp * tanh((y - pr.y_mid - P[(long long)x * g.ly + y]) / pr.width);
-    const double r0 = pr.p0 / T0;
-    S* p = buf + g.origin + (long long)x * g.cs + y;
-#pragma unroll
-    for (int l = 0; l < NPOP; ++l) p[(size_t)l * g.ps] = (S)feq_pop<Store<S>::shifted>(l, r0, 0.0, 0.0, T0);
+    init_site<S, NT>(buf, g, x, y, pr.p0 / T0, 0.0, 0.0, T0, wall_rho);
 }
 
 // rho, u, T of eq. (2) in FP64.  Shifted storage uses the deviation form
 // rho = 1 + sum d, T - 1 = (sum (x2 - 2) d) / (2 rho) - u2 / 2.
-template <typename S>
-__device__ __forceinline__ void site_macros(const S* p, long long plane, double& rho, double& ux, double& uy, double& T)
+template <typename S, bool NT = false>
+__device__ __forceinline__ void site_macros(const S* col, unsigned yb, long long plane, double& rho, double& ux, double& uy,
+                                            double& T)
 {
     double f[NPOP];
 #pragma unroll
-    for (int l = 0; l < NPOP; ++l) f[l] = (double)p[(size_t)l * plane];
+    for (int l = 0; l < NPOP; ++l) f[l] = (double)(NT ? ld_nt(col + (size_t)l * plane, yb) : ld_at(col + (size_t)l * plane, yb));
     double m0, sx, sy, s2;
     hop_moments<double>(f, m0, sx, sy, s2);
     if (Store<S>::shifted) {
@@ -550,7 +573,9 @@ __device__ __forceinline__ void site_macros(const S* p, long long plane, double&
     }
 }
 
-template <typename S>
+// NT: non-temporal loads (large lattices: 1024 x 2048 FP64 109 us against 122).
+// The fields' rows start anywhere, so their stores are left to the L2 to merge.
+template <typename S, bool NT>
 __global__ __launch_bounds__(SITE_THREADS) void k_macros(const S* __restrict__ buf, Geo g, double* __restrict__ rho,
                                                       double* __restrict__ ux, double* __restrict__ uy, double* __restrict__ T)
 {
@@ -558,9 +583,10 @@ __global__ __launch_bounds__(SITE_THREADS) void k_macros(const S* __restrict__ b
     const int x = sb.x, y = sb.y;
     if (y >= g.ly) return;
     double r, vx, vy, t;
-    site_macros<S>(buf + g.origin + (long long)x * g.cs + y, g.ps, r, vx, vy, t);
-    const long long s = (long long)x * g.ly + y;
-    rho[s] = r; ux[s] = vx; uy[s] = vy; T[s] = t;
+    site_macros<S, NT>(buf + g.origin + (long long)x * g.cs, (unsigned)y * (unsigned)sizeof(S), g.ps, r, vx, vy, t);
+    const long long s = (long long)x * g.ly;
+    const unsigned yd = (unsigned)y * 8u;
+    st_at(rho + s, yd, r); st_at(ux + s, yd, vx); st_at(uy + s, yd, vy); st_at(T + s, yd, t);
 }
 
 // canonical [37][lx][ly] <-> padded: 16-byte vectors, one per thread.  A
@@ -663,17 +689,25 @@ __device__ __forceinline__ void block_sum_store(double (&v)[N], double* __restri
 
 constexpr int RED_BLOCKS = 1024;
 
-template <typename S>
+// NT: non-temporal loads, for large arrays whose waves read whole lines (ly a
+// multiple of 64: 2048 x 4096 FP32 184 us against 205, but 1080 x 4095 FP32 128
+// against 118).  The site index walks without divisions.
+template <typename S, bool NT>
 __global__ __launch_bounds__(256) void k_conservation_partial(const S* __restrict__ buf, Geo g, double* __restrict__ partials)
 {
     double acc[4] = {0.0, 0.0, 0.0, 0.0};
     const long long n = (long long)g.lx * g.ly;
-    for (long long i = (long long)blockIdx.x * 256 + threadIdx.x; i < n; i += (long long)gridDim.x * 256) {
-        const int x = (int)(i / g.ly), y = (int)(i % g.ly);
+    const long long first = (long long)blockIdx.x * 256 + threadIdx.x, step = (long long)gridDim.x * 256;
+    const int dx = (int)(step / g.ly), dy = (int)(step % g.ly);
+    int x = (int)(first / g.ly), y = (int)(first % g.ly);
+    for (long long i = first; i < n; i += step) {
         const S* p = buf + g.origin + (long long)x * g.cs + y;
+        x += dx;
+        y += dy;
+        if (y >= g.ly) { y -= g.ly; ++x; }
         double f[NPOP];
 #pragma unroll
-        for (int l = 0; l < NPOP; ++l) f[l] = (double)p[(size_t)l * g.ps];
+        for (int l = 0; l < NPOP; ++l) f[l] = (double)(NT ? __builtin_nontemporal_load(p + (size_t)l * g.ps) : p[(size_t)l * g.ps]);
         double m0, sx, sy, s2;
         hop_moments<double>(f, m0, sx, sy, s2);
         acc[0] += Store<S>::shifted ? 1.0 + m0 : m0;

@@ -43,3 +43,39 @@ def test_canonical_copies_and_snapshots(lx, ly, precision, layout):
         assert torch.equal(other.get_pops(), f)
         assert torch.equal(other.get_state(), lat.get_state())
         raw.fill_(0x5A)
+
+
+# both sides of the streaming bound of the read-outs and initial states, and of
+# the totals' row condition
+@pytest.mark.parametrize("lx,ly", [(7, 7), (33, 70), (1024, 1024), (1024, 1030)])
+@pytest.mark.parametrize("precision", ["fp64", "fp32"])
+def test_initial_states_and_read_outs(lx, ly, precision):
+    """The wall densities that init leaves are those of a state set from its
+    populations (bitwise: one sum in one order), and macros and totals are the
+    moments of the populations: sums of 37 terms in FP64 differ by at most
+    37 ulp between summation orders, totals of N sites by sqrt(N) of those."""
+    say(f"initial states {lx}x{ly} {precision}")
+    import oracle
+    lat, other = (Lattice(lx, ly, TAU, G, TB, TT, precision=precision, device=DEV) for _ in range(2))
+    g = torch.Generator(device=DEV).manual_seed(3)
+    P = torch.rand((lx, ly), generator=g, device=DEV, dtype=torch.float64)
+    lat.init_rt(P)
+    for _ in range(2):
+        other.set_pops(lat.get_pops())
+        assert torch.equal(lat.get_state(), other.get_state())
+        lat.init(1.0 + 0.1 * P, 0.02 * P, -0.01 * P, 1.0 + 0.05 * P)
+    f = lat.get_pops().double()
+    if precision == "fp32":
+        f = f + torch.tensor(oracle.weights(), device=DEV)[:, None, None]
+    ex, ey = oracle.velocity_table()
+    c = oracle.scale_c()
+    xi = [torch.tensor([c * float(v) for v in e], dtype=torch.float64, device=DEV)[:, None, None] for e in (ex, ey)]
+    rho = f.sum(0)
+    j = [(x * f).sum(0) for x in xi]
+    en = ((xi[0] ** 2 + xi[1] ** 2) * f).sum(0)
+    T = (en / rho - (j[0] ** 2 + j[1] ** 2) / rho ** 2) / 2
+    tol = 37 * 2.3e-16 * 10          # sum of |terms| over the sum: at most 10 for the energy
+    for a, b in zip(lat.macros(), (rho, j[0] / rho, j[1] / rho, T)):
+        assert float((a - b).abs().max()) <= tol
+    tot = torch.stack([rho.sum(), j[0].sum(), j[1].sum(), en.sum()])
+    assert bool(((lat.conservation() - tot).abs() <= tol * lx * ly).all())
