@@ -78,7 +78,8 @@ typedef enum { LBM_FP64 = 0, LBM_FP32_SHIFTED = 1, LBM_FP32_SHIFTED_F32SUMS = 2 
 typedef enum { LBM_Y_WALLS = 0, LBM_Y_PERIODIC = 1 } lbm_ybc;
 /* How x-periodicity reaches propagate: wrap the source column index inside the
  * kernel, or first copy 3-column halos (the in-GPU form of the paper's halo
- * exchange between lattice regions, section 5). Results are identical. */
+ * exchange between lattice regions, section 5). Passes of two fused steps
+ * (lbm_step) wrap the index in either mode. Results are identical. */
 typedef enum { LBM_X_WRAP = 0, LBM_X_HALO = 1 } lbm_xmode;
 /* lbm_step as three kernels (propagate, bc, collide) or as one fused
  * gather-collide pass (eq. (4) evaluated per site). Results are identical up
@@ -159,9 +160,9 @@ lbm_status lbm_bc(lbm_ctx* ctx);
  * moments (eq. (2)), gravity shift, equilibrium, f <- f + (f^eq - f)/tau. */
 lbm_status lbm_collide(lbm_ctx* ctx);
 /* n >= 0 times (propagate, bc, collide), split or fused per step_kind.
- * Fused steps with LBM_X_WRAP run two to a pass over memory where n >= 4
- * allows (in groups of four steps); the results are bitwise those of n single
- * steps, for lbm_bc after it too.
+ * Fused steps run two to a pass over memory where n >= 4 allows (in groups of
+ * four steps); the results are bitwise those of n single steps, for lbm_bc
+ * after it too.
  * It only launches kernels on the context's stream, so it can be captured
  * into a HIP graph there (after at least one eager step).  A replay repeats
  * the captured launches with the buffers they were captured with: capture an
@@ -188,9 +189,8 @@ lbm_status lbm_set_state(lbm_ctx* ctx, const void* src);
  * 256-byte aligned, not overlapping, in the format of lbm_get_state (dst
  * receives the new state's wall densities too, so it can serve as the next
  * source or as an lbm_adjoint_step snapshot).  The sites and wall densities
- * of src_state are only read; its padding (y ghost rows, x halo columns) is
- * refreshed in place when the boundary mode needs it.  The context's own
- * population buffers are not touched.  Lets a checkpointed replay run from
+ * of src_state are only read; its padding (x halo columns) is refreshed in
+ * place for LBM_X_HALO.  The context's own population buffers are not touched.  Lets a checkpointed replay run from
  * snapshot to snapshot instead of stepping the context and copying its state
  * out. */
 lbm_status lbm_step_state(lbm_ctx* ctx, void* src_state, void* dst_state);

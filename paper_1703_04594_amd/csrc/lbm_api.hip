@@ -154,6 +154,7 @@ void set_collide_args(lbm_ctx* c)
     c->cargs.tau_g = tau * g;
     c->cargs.grav_th = tau * (1.0 - tau) * g * g / 2.0;
     c->cargs.g = g;
+    c->cargs.g_over_c = g / C;
     c->cargs.g_f = (float)g;
     c->cargs.omega_f = (float)c->cargs.omega;
     c->cargs.tau_g_f = (float)c->cargs.tau_g;
@@ -190,13 +191,14 @@ lbm_status launch_propagate(lbm_ctx* c, const S* src, S* dst)
 }
 
 template <typename S>
-lbm_status launch_pre_stream(lbm_ctx* c, S* src)
+lbm_status launch_pre_stream(lbm_ctx* c, S* src, bool ghosts)
 {
-    // halos the pull of the current buffer needs: y ghost rows if periodic,
-    // then x halo columns (whole padded columns, so corners follow).
+    // halos the pull of the current buffer needs: y ghost rows if periodic
+    // and asked for, then x halo columns (whole padded columns, so corners
+    // follow).
     const Geo& g = c->pl.geo;
-    if (c->p.ybc == LBM_Y_PERIODIC) {
-        dim3 grid((g.lx * 6 + 255) / 256, NPOP);
+    if (ghosts && c->p.ybc == LBM_Y_PERIODIC) {
+        dim3 grid((g.lx * 3 + 255) / 256, NPOP);
         hipLaunchKernelGGL((k_fill_y_ghosts<S>), grid, dim3(256), 0, c->stream, src, g);
         lbm_status s = check_launch(c, "fill_y_ghosts");
         if (s) return s;
@@ -235,7 +237,7 @@ lbm_status do_propagate(lbm_ctx* c)
 {
     S* src = (S*)c->buf(c->cur);
     S* dst = (S*)c->buf(1 - c->cur);
-    lbm_status s = launch_pre_stream<S>(c, src);
+    lbm_status s = launch_pre_stream<S>(c, src, true);
     if (s) return s;
     s = launch_propagate<S>(c, src, dst);
     if (s) return s;
@@ -350,7 +352,7 @@ lbm_status do_step_fused(lbm_ctx* c)
 {
     S* src = (S*)c->buf(c->cur);
     S* dst = (S*)c->buf(1 - c->cur);
-    lbm_status s = launch_pre_stream<S>(c, src);
+    lbm_status s = launch_pre_stream<S>(c, src, false);
     if (s) return s;
     const bool walls = c->p.ybc == LBM_Y_WALLS;
     if (walls) {
@@ -401,11 +403,9 @@ lbm_status do_two_steps(lbm_ctx* c)
 {
     S* src = (S*)c->buf(c->cur);
     S* dst = (S*)c->buf(1 - c->cur);
-    lbm_status s = launch_pre_stream<S>(c, src);
-    if (s) return s;
     const bool walls = c->p.ybc == LBM_Y_WALLS;
     if (walls) {
-        s = ensure_wall_density<S>(c, c->cur);
+        lbm_status s = ensure_wall_density<S>(c, c->cur);
         if (s) return s;
     }
     const double* wr = c->wall_rho(c->wr_cur);
@@ -423,7 +423,7 @@ lbm_status do_two_steps(lbm_ctx* c)
         if (walls) launch_two_step<S, true, true>(c, src, dst, wr, mid, wo);
         else launch_two_step<S, false, true>(c, src, dst, wr, mid, wo);
     }
-    s = check_launch(c, "two_steps");
+    const lbm_status s = check_launch(c, "two_steps");
     if (s) return s;
     c->cur = 1 - c->cur;
     c->have_prev = true;
@@ -598,7 +598,7 @@ lbm_status do_step_state(lbm_ctx* c, char* src, char* dst)
 {
     S* sb = (S*)src;
     S* db = (S*)dst;
-    lbm_status s = launch_pre_stream<S>(c, sb);   // padding of the source only
+    lbm_status s = launch_pre_stream<S>(c, sb, false);   // padding of the source only
     if (s) return s;
     const bool walls = c->p.ybc == LBM_Y_WALLS;
     const double* wr = walls ? (const double*)(src + c->pl.buf_bytes) : nullptr;
@@ -779,7 +779,7 @@ lbm_status lbm_create(const lbm_params* p, void* dev_workspace, size_t bytes, vo
         c->fused_threads = fl.threads;
         c->fused_lds = fl.lds;
         c->dev_stores = dev_stores_for(site_grid(pl.geo).x, ncu);
-        if (p->step_kind == LBM_STEP_FUSED && p->xmode == LBM_X_WRAP)
+        if (p->step_kind == LBM_STEP_FUSED)
             c->two = p->precision == LBM_FP64 ? choose_two_step<double>(pl.geo, ncu, max_lds, p->ybc == LBM_Y_WALLS)
                                               : choose_two_step<float>(pl.geo, ncu, max_lds, p->ybc == LBM_Y_WALLS);
         if ((size_t)site_grid(pl.geo).x >= (size_t)FUSED_FP64_CAP_MIN_BLOCKS_PER_CU * (size_t)ncu) {

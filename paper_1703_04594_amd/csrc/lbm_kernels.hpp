@@ -301,17 +301,20 @@ __global__ __launch_bounds__(256) void k_fill_x_halo(S* __restrict__ buf, Geo g)
     p[(long long)to * g.cs] = p[(long long)from * g.cs];
 }
 
-// y ghost rows for LBM_Y_PERIODIC: rows [-3, 0) <- [ly-3, ly), [ly, ly+3) <- [0, 3).
+// y ghost rows of LBM_Y_PERIODIC that k_propagate reads (the kernels that
+// gather per site wrap the row instead): below row 0 for e_y > 0, behind row
+// ly - 1 for e_y < 0, |e_y| of them.
 template <typename S>
 __global__ __launch_bounds__(256) void k_fill_y_ghosts(S* __restrict__ buf, Geo g)
 {
     const int l = blockIdx.y;
+    const int ey = c_hops.ey[l], n = ey > 0 ? ey : -ey;
     const int t = blockIdx.x * 256 + threadIdx.x;
-    if (t >= g.lx * 6) return;
-    const int x = t / 6, r = t % 6;
+    if (t >= g.lx * n) return;
+    const int x = t / n, r = t % n;
     S* p = buf + (size_t)l * g.ps + g.origin + (long long)x * g.cs;
-    if (r < 3) p[r - 3] = p[g.ly - 3 + r];
-    else p[g.ly + r - 3] = p[r - 3];
+    if (ey > 0) p[-1 - r] = p[g.ly - 1 - r];
+    else p[g.ly + r] = p[r];
 }
 
 // Density of the 3 rows next to each wall (FP64), for the wall rule.
@@ -360,18 +363,24 @@ __global__ __launch_bounds__(256) void k_bc_apply(S* __restrict__ dst, Geo g, co
 // ---------------------------------------------------------------------------
 
 // Density of a site from its just-written populations, summed in population
-// order in FP64 exactly as k_wall_density sums them, into the wall-density
-// table of the next step (rows 0..2 and ly-3..ly-1 only).
+// order in FP64 exactly as k_wall_density sums them.
+template <typename S, typename Cc>
+__device__ __forceinline__ double stored_density(const Cc (&f)[NPOP])
+{
+    double r = 0.0;
+#pragma unroll
+    for (int l = 0; l < NPOP; ++l) r += (double)(S)f[l];
+    return Store<S>::shifted ? 1.0 + r : r;
+}
+// The same into the wall-density table of the next step (rows 0..2 and
+// ly-3..ly-1 only).
 template <typename S, typename Cc>
 __device__ __forceinline__ void store_wall_density(const Cc (&f)[NPOP], const Geo& g, int x, int y,
                                                    double* __restrict__ wall_rho_out)
 {
     if (y < 3 || y >= g.ly - 3) {
-        double r = 0.0;
-#pragma unroll
-        for (int l = 0; l < NPOP; ++l) r += (double)(S)f[l];
         const int wk = y < 3 ? y : 3 + (g.ly - 1 - y);
-        wall_rho_out[wk * g.lx + x] = Store<S>::shifted ? 1.0 + r : r;
+        wall_rho_out[wk * g.lx + x] = stored_density<S>(f);
     }
 }
 
@@ -466,6 +475,9 @@ __global__ __launch_bounds__(T) void k_step_fused(const S* __restrict__ src, S* 
     const int x = sb.x, y = sb.y;
     if (y >= g.ly) return;
     const unsigned yb = (unsigned)y * (unsigned)sizeof(S);
+    unsigned yp[7];   // byte offsets of rows y - 3 .. y + 3 of a lattice without walls
+#pragma unroll
+    for (int k = 0; k < 7; ++k) yp[k] = (unsigned)wrap_x(y + k - 3, g.ly) * (unsigned)sizeof(S);
     Cc f[NPOP];
     // FP64: the 37 gathers are issued at raised wave priority, so a wave that
     // reaches them is not held behind other waves' collide arithmetic
@@ -475,7 +487,8 @@ __global__ __launch_bounds__(T) void k_step_fused(const S* __restrict__ src, S* 
     for (int l = 0; l < NPOP; ++l) {
         int xs = x - EX[l];
         if (WRAP) xs = wrap_x(xs, g.lx);
-        f[l] = (Cc)ld_at(src + (size_t)l * g.ps + g.origin + (long long)xs * g.cs - EY[l], yb);
+        const S* col = src + (size_t)l * g.ps + g.origin + (long long)xs * g.cs;
+        f[l] = (Cc)(WALLS ? ld_at(col - EY[l], yb) : ld_at(col, yp[3 - EY[l]]));
     }
     if constexpr (sizeof(S) == 8) {
         __builtin_amdgcn_sched_barrier(0);

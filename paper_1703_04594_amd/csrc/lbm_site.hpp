@@ -180,6 +180,7 @@ struct CollideArgs {
     double tau_g;    // tau * g_y   (velocity shift)
     double grav_th;  // tau (1 - tau) g_y^2 / 2   (temperature shift)
     double g;        // g_y
+    double g_over_c; // g_y / c
     float omega_f, tau_g_f, grav_th_f, g_f;
 };
 
@@ -300,8 +301,12 @@ __device__ __forceinline__ void collide_site(C (&f)[NPOP], const CollideArgs& ar
             hop_moments_wide(f, M0, MX, MY, M2);
             d0 = (C)(m0d - M0);
             dx = (C)(sxd - MX);
-            dy = (C)(fma_(1.0 + m0d, args.g / cscale<double>(), syd) - MY);
-            d2 = (C)(s2d + (double)(rho * sum_of_products(C(2) * g, uy0, g, g) / c2) - M2);
+            dy = (C)(fma_(1.0 + m0d, args.g_over_c, syd) - MY);
+            // the quotient by c^2, in FP32: a product in FP64 rounds to it, as
+            // no quotient of two FP32 numbers lies within 2^-49 of itself of
+            // a rounding boundary, and the product is off by 2^-52 at most
+            const float work = (float)((double)(rho * sum_of_products(C(2) * g, uy0, g, g)) * (1.0 / (double)c2scale<C>()));
+            d2 = (C)(s2d + (double)work - M2);
         } else {
             C M0, MX, MY, M2;
             hop_moments<C>(f, M0, MX, MY, M2);

@@ -66,47 +66,63 @@ constexpr WallHops make_wall_hops()
 }
 constexpr WallHops WH = make_wall_hops();
 
-// f with the wall slots of row y replaced: v[j] is the value f^eq_l(1, 0,
-// T_wall) rho_mirror of hop j of WH at this lane's wall (any value where the
-// slot is not a wall slot).
-template <typename S, typename Cc>
-__device__ __forceinline__ void put_wall_slots(Cc (&f)[NPOP], int y, int ly, const double (&ew)[NWS], const double (&rho)[NWS])
+// The wall slots of a site r rows from wall W (r < 3), replaced in f by
+// f^eq_l(1, 0, T_wall) times the density rho(ex, k) of their mirror site, k
+// rows from the wall and ex columns back.  The densities are all read before
+// the first is used.
+template <typename S, int W, typename Cc>
+__device__ __forceinline__ void put_wall_slots(Cc (&f)[NPOP], int r, const WallTable& wt, const double (&d)[NWS])
 {
 #pragma unroll
     for (int j = 0; j < NWS; ++j) {
-        double v = ew[j] * rho[j];
-        if (Store<S>::shifted) v -= W_SHELL[SHELL[WH.bot[j]]];
-        if (y < WH.en[j]) f[WH.bot[j]] = (Cc)v;
-        if (ly - 1 - y < WH.en[j]) f[WH.top[j]] = (Cc)v;
+        const int l = W == 0 ? WH.bot[j] : WH.top[j];
+        double v = wt.ew[W][l] * d[j];
+        if (Store<S>::shifted) v -= W_SHELL[SHELL[l]];
+        f[l] = r < WH.en[j] ? (Cc)v : f[l];
     }
 }
 
-// Density of a site in FP64 from its stored populations (the order of
-// k_wall_density).
-template <typename S, typename Cc>
-__device__ __forceinline__ double stored_density(const Cc (&f)[NPOP])
+// Buffer accesses: block-uniform base, per-lane and uniform 32-bit byte offsets.
+template <typename S>
+__device__ __forceinline__ S buf_load(__amdgpu_buffer_rsrc_t r, int voff, int soff)
 {
-    double r = 0.0;
-#pragma unroll
-    for (int l = 0; l < NPOP; ++l) r += (double)(S)f[l];
-    return Store<S>::shifted ? 1.0 + r : r;
+    if constexpr (sizeof(S) == 4) return __builtin_bit_cast(S, __builtin_amdgcn_raw_buffer_load_b32(r, voff, soff, 0));
+    else return __builtin_bit_cast(S, __builtin_amdgcn_raw_buffer_load_b64(r, voff, soff, 0));
+}
+template <typename S, int POL>
+__device__ __forceinline__ void buf_store(S v, __amdgpu_buffer_rsrc_t r, int voff, int soff)
+{
+    if constexpr (sizeof(S) == 4) __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, v), r, voff, soff, POL);
+    else __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2_t, v), r, voff, soff, POL);
+}
+template <typename S>
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t buf_of(S* base)
+{
+    return __builtin_amdgcn_make_buffer_rsrc((void*)base, 0, RAW_BUFFER_ALL_BYTES, RAW_BUFFER_WORD3);
 }
 
 // ---------------------------------------------------------------------------
 // Tiles.  One thread per site of the first step (the tile and three rows and
 // columns around it); the tile's own sites, as many threads, run the second.
+// Without walls the gather wraps the row as it does the column, so a pass needs
+// no ghost rows (512 x 512: 2.6-3.6 us per pass for the launch that filled them).
 // What bounds a pass: on the smallest lattices the chain of one load, two
-// collisions and an LDS exchange (256 x 128 FP64: 14 us per two steps against
-// 17-18 us in single steps); above, the first step's work on the rings
-// (512 x 512: 41 us against 55 us FP64, 32 against 36 us FP32).  Stores are
-// plain: the next pass reads them from the caches (512 x 512 FP64: 41 us
-// against 51 us with non-temporal ones).
+// collisions and an LDS exchange (256 x 128 FP64: 11.7 us per two steps against
+// 17 us in single steps); above, the first step's work on the rings (512 x 512:
+// 33.5 us against 55 us FP64, 28 against 36 us FP32).
+// The buffer accesses keep one SGPR offset running over the populations: with
+// 64-bit column addresses 512 x 512 FP64 took 40.3 us, FP32 31.1.  The wall
+// densities are read ahead of the populations (behind them 128 x 128 FP64
+// +0.4 us).  Stores are plain: the next pass reads them from the caches (with
+// non-temporal ones 512 x 512 FP64 took 10 us more).  With FP32 sums 80
+// registers are enough for six waves per SIMD (384 x 384 without walls: 18.9 us
+// against 21.1 with 128); the FP64 sums would spill (27 us against 22).
 // ---------------------------------------------------------------------------
 template <int TX, int TY>
 constexpr int tile_threads() { return ((TX + 6) * (TY + 6) + 63) / 64 * 64; }
 
 template <typename S, bool WALLS, bool WIDE, int TX, int TY>
-__global__ __launch_bounds__((tile_threads<TX, TY>()), 4) void k_twostep_tile(
+__global__ __launch_bounds__((tile_threads<TX, TY>()), WIDE ? 4 : 6) void k_twostep_tile(
     const S* __restrict__ src, S* __restrict__ dst, Geo g, CollideArgs args, const double* __restrict__ wall_rho,
     WallTable wt, double* __restrict__ wall_mid, double* __restrict__ wall_rho_out)
 {
@@ -118,6 +134,7 @@ __global__ __launch_bounds__((tile_threads<TX, TY>()), 4) void k_twostep_tile(
     const int x0 = L / nty * TX, y0 = L % nty * TY;
     const int x1 = min(x0 + TX, g.lx), y1 = min(y0 + TY, g.ly);
     const int t = (int)threadIdx.x;
+    const int stride = (int)(g.ps * (long long)sizeof(S));   // between populations (the whole buffer is below 2 GB)
     {
         const int ax = t / (TY + 6), ay = t % (TY + 6);
         const int X = x0 - 3 + ax;
@@ -130,24 +147,32 @@ __global__ __launch_bounds__((tile_threads<TX, TY>()), 4) void k_twostep_tile(
         }
         if (on) {
             Cc f[NPOP];
-            unsigned off[7];
+            int xs[7];   // columns X - 3 .. X + 3
 #pragma unroll
-            for (int k = 0; k < 7; ++k)
-                off[k] = (unsigned)(((long long)wrap_x(X - (k - 3), g.lx) * g.cs + y) * (long long)sizeof(S));
-            const bool near = WALLS && (y < 3 || y >= g.ly - 3);
-            const int wall = y < 3 ? 0 : 1, r = wall ? g.ly - 1 - y : y;
-            double rho[NWS], ew[NWS];
-            if (near) {   // loaded beside the populations, not behind them
+            for (int k = 0; k < 7; ++k) xs[k] = wrap_x(X + k - 3, g.lx);
+            int ys[7];   // rows y - 3 .. y + 3 of a lattice without walls, as offsets from the base below
 #pragma unroll
-                for (int j = 0; j < NWS; ++j) {
-                    ew[j] = wall ? wt.ew[1][WH.top[j]] : wt.ew[0][WH.bot[j]];
-                    rho[j] = wall_rho[(wall * 3 + max(WH.en[j] - 1 - r, 0)) * g.lx + wrap_x(X - WH.ex[j], g.lx)];
-                }
+            for (int k = 0; k < 7; ++k) ys[k] = 3 + wrap_x(y + k - 3, g.ly);
+            const __amdgpu_buffer_rsrc_t rs = buf_of(src + g.origin - 3);
+            const int r = y < 3 ? y : g.ly - 1 - y;   // rows from the wall
+            const bool near = WALLS && r < 3;
+            double d[NWS];
+            if (near) {   // read ahead of the populations, not behind them
+                const double* w0 = wall_rho + (y < 3 ? 0 : 3 * g.lx);
+#pragma unroll
+                for (int j = 0; j < NWS; ++j) d[j] = w0[max(WH.en[j] - 1 - r, 0) * g.lx + xs[3 - WH.ex[j]]];
             }
+            int soff = 0;
 #pragma unroll
-            for (int l = 0; l < NPOP; ++l)
-                f[l] = (Cc)ld_at(src + (size_t)l * g.ps + g.origin - EY[l], off[EX[l] + 3]);
-            if (near) put_wall_slots<S>(f, y, g.ly, ew, rho);
+            for (int l = 0; l < NPOP; ++l) {
+                const int row = WALLS ? y + 3 - EY[l] : ys[3 - EY[l]];
+                f[l] = (Cc)buf_load<S>(rs, (xs[3 - EX[l]] * (int)g.cs + row) * (int)sizeof(S), soff);
+                soff += stride;
+            }
+            if (near) {
+                if (y < 3) put_wall_slots<S, 0>(f, r, wt, d);
+                else put_wall_slots<S, 1>(f, r, wt, d);
+            }
             collide_site<Cc, Store<S>::shifted, WIDE>(f, args);
             const int ox = ax - 3, oy = ay - 3;
             const int p = ox * TY + oy;
@@ -157,8 +182,9 @@ __global__ __launch_bounds__((tile_threads<TX, TY>()), 4) void k_twostep_tile(
                     post[l][p + EX[l] * TY + EY[l]] = (S)f[l];
             if (near) {
                 const double d = stored_density<S>(f);
-                wr[wall * 3 + r][ax] = d;
-                if (X >= x0 && X < x1) wall_mid[(wall * 3 + r) * g.lx + X] = d;
+                const int wk = y < 3 ? r : 3 + r;
+                wr[wk][ax] = d;
+                if (X >= x0 && X < x1) wall_mid[wk * g.lx + X] = d;
             }
         }
     }
@@ -170,22 +196,26 @@ __global__ __launch_bounds__((tile_threads<TX, TY>()), 4) void k_twostep_tile(
             Cc f[NPOP];
 #pragma unroll
             for (int l = 0; l < NPOP; ++l) f[l] = (Cc)post[l][t];
-            const bool near = WALLS && (y < 3 || y >= g.ly - 3);
-            const int wall = y < 3 ? 0 : 1, r = wall ? g.ly - 1 - y : y;
+            const int r = y < 3 ? y : g.ly - 1 - y;
+            const bool near = WALLS && r < 3;
             if (near) {
-                double rho[NWS], ew[NWS];
+                const int w0 = WALLS && y >= 3 ? 3 : 0;
+                double d[NWS];
 #pragma unroll
-                for (int j = 0; j < NWS; ++j) {
-                    ew[j] = wall ? wt.ew[1][WH.top[j]] : wt.ew[0][WH.bot[j]];
-                    rho[j] = wr[WALLS ? wall * 3 + max(WH.en[j] - 1 - r, 0) : 0][ox + 3 - WH.ex[j]];
-                }
-                put_wall_slots<S>(f, y, g.ly, ew, rho);
+                for (int j = 0; j < NWS; ++j) d[j] = wr[WALLS ? w0 + max(WH.en[j] - 1 - r, 0) : 0][ox + 3 - WH.ex[j]];
+                if (y < 3) put_wall_slots<S, 0>(f, r, wt, d);
+                else put_wall_slots<S, 1>(f, r, wt, d);
             }
+            const __amdgpu_buffer_rsrc_t rs = buf_of(dst + g.origin);
+            const int off = (X * (int)g.cs + y) * (int)sizeof(S);
             collide_site<Cc, Store<S>::shifted, WIDE>(f, args);
-            const unsigned off = (unsigned)(((long long)X * g.cs + y) * (long long)sizeof(S));
+            int soff = 0;
 #pragma unroll
-            for (int l = 0; l < NPOP; ++l) st_at(dst + (size_t)l * g.ps + g.origin, off, (S)f[l]);
-            if (near) wall_rho_out[(wall * 3 + r) * g.lx + X] = stored_density<S>(f);
+            for (int l = 0; l < NPOP; ++l) {
+                buf_store<S, 0>((S)f[l], rs, off, soff);
+                soff += stride;
+            }
+            if (near) wall_rho_out[(y < 3 ? r : 3 + r) * g.lx + X] = stored_density<S>(f);
         }
     }
 }
@@ -231,24 +261,6 @@ constexpr int ring_base(int ex)
     return n;
 }
 static_assert(ring_base(4) == 4 * NPOP, "rings hold four columns per population on average");
-
-template <typename S>
-__device__ __forceinline__ S buf_load(__amdgpu_buffer_rsrc_t r, int voff, int soff)
-{
-    if constexpr (sizeof(S) == 4) return __builtin_bit_cast(S, __builtin_amdgcn_raw_buffer_load_b32(r, voff, soff, 0));
-    else return __builtin_bit_cast(S, __builtin_amdgcn_raw_buffer_load_b64(r, voff, soff, 0));
-}
-template <typename S>
-__device__ __forceinline__ void buf_store(S v, __amdgpu_buffer_rsrc_t r, int voff, int soff)
-{
-    if constexpr (sizeof(S) == 4) __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, v), r, voff, soff, STORE_CPOL_NT_SC1);
-    else __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2_t, v), r, voff, soff, STORE_CPOL_NT_SC1);
-}
-template <typename S>
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t buf_of(S* base)
-{
-    return __builtin_amdgcn_make_buffer_rsrc((void*)base, 0, RAW_BUFFER_ALL_BYTES, RAW_BUFFER_WORD3);
-}
 
 // Launch of the march over an lx x ly lattice: strips of ny rows, cut along x
 // into segments, one block each, all blocks on the GPU at once.
@@ -392,6 +404,9 @@ __global__ __launch_bounds__(2 * MarchShape<S>::waves * 64) void k_twostep_march
         const int wall = y < 3 ? 0 : 1, wr = wall ? g.ly - 1 - y : y;   // rows from the wall
         const bool near = WALLS && on && wr < 3;
         int vo = y * (int)sizeof(S);
+        int vp[7];   // byte offsets of rows y - 3 .. y + 3 of a lattice without walls
+#pragma unroll
+        for (int k = 0; k < 7; ++k) vp[k] = (3 + wrap_x(y + k - 3, g.ly)) * (int)sizeof(S);
         // ring row of this lane; lanes without a site store to the padding
         const int rw = 6 + (on ? r : NY + 5);
         const S* cp[7];   // source columns X - 3 .. X + 3 of the first-step column X, three rows down
@@ -414,7 +429,7 @@ __global__ __launch_bounds__(2 * MarchShape<S>::waves * 64) void k_twostep_march
 #pragma unroll
             for (int l = 0; l < NPOP; ++l) {
                 if (l < lo || l >= hi) continue;
-                f[l] = (Cc)buf_load<S>(rs[3 - EX[l]], vo + (3 - EY[l]) * (int)sizeof(S), soff);
+                f[l] = (Cc)buf_load<S>(rs[3 - EX[l]], WALLS ? vo + (3 - EY[l]) * (int)sizeof(S) : vp[3 - EY[l]], soff);
                 soff += stride8;
             }
         };
@@ -546,7 +561,7 @@ __global__ __launch_bounds__(2 * MarchShape<S>::waves * 64) void k_twostep_march
                     if (i + 1 < ncol) lds_barrier();   // the ring may be overwritten
                     __builtin_amdgcn_sched_barrier(0);
                 },
-                [&](int l) { buf_store((S)q[l], rs, ob, l * stride8); });
+                [&](int l) { buf_store<S, STORE_CPOL_NT_SC1>((S)q[l], rs, ob, l * stride8); });
 #pragma unroll
             for (int l = 0; l < NPOP; ++l) {
                 __builtin_amdgcn_sched_group_barrier(0x2, sizeof(S) == 8 ? 9 : 4, 0);
@@ -568,20 +583,25 @@ __global__ __launch_bounds__(2 * MarchShape<S>::waves * 64) void k_twostep_march
 enum TwoStepKind { TWO_STEP_NONE = 0, TWO_STEP_TILE_8X8, TWO_STEP_TILE_8X16, TWO_STEP_TILE_16X16, TWO_STEP_MARCH };
 struct TwoStep { TwoStepKind kind; MarchLaunch march; };
 
-// The march pays where its blocks' lanes and columns are mostly used: sites
-// over (columns the slowest block steps x rows x CUs) of at least 0.55.
-// Measured, us per two steps, march / tiles / single steps, with that share:
-// FP64 512x512 (0.48) 51 / 41 / 55, 301x1030 (0.54) 53 / 44 / 82, 768x768
-// (0.64) 88 / 107 / 141, 1024x1024 (0.72) 136 / 172 / 239, 2048x4096 (0.84)
-// 895 / 1287 / 1660; FP32 768x768 (0.44) 70 / 56 / 76, 100x4096 (0.48) 44 / 43
-// / 54, 1024x1024 (0.57) 98 / 125 / 123, 2048x4096 (0.83) 554 / 957 / 862.
-// Below, tiles; in FP32, whose collisions are the larger part of a step, only
-// up to 12 x 256 sites per CU (above, single steps: see 1024x1024).
+// Tiles where both buffers stay in the 256 MB Infinity Cache, which covers what
+// they read twice; beyond it the march, where its blocks' lanes and columns are
+// mostly used: sites over (columns the slowest block steps x rows x CUs) of at
+// least 0.55.  Measured, us per step, march / tiles (padded buffers in MB, with
+// walls unless noted): FP64 400x1000 (242) 29.7 / 28.2, 640x640 (239) 32.9 /
+// 28.6, 680x680 (266) 37.6 / 36.5, without walls 33.7 / 35.6, 720x720 (296) 39.5 /
+// 42.3, 1024x1024 (592) 67 / 79; FP32 850x850 (213) 31.9 / 31.7 and with FP32
+// sums 29.5 / 25.4, 900x900 (237) 38.6 / 34.9, 930x930 (254) 41.7 / 42.2,
+// 1024x1024 (306) 50 / 58.  Beyond the cache and below that share tiles still
+// gain on single steps in FP64 (2048x4096: 1287 us per two steps against 1660);
+// in FP32, whose collisions are the larger part of a step, up to 16 x 256 sites
+// per CU (1024x1024: 115 against 123; 2048x4096: 957 against 862).
 // The smallest tiles are taken while they leave no CU with more than one
-// (FP64: 128x128 11.4 us with 8x8, 12.6 with 8x16, 14.7 with 16x16; 256x128
-// 15.5, 13.2, 15.3; 256x256 22, 19, 17).
+// (us per step, 8x8 / 8x16 / 16x16: FP64 128x128 4.7 / - / 6.2, 256x128 6.3 /
+// 5.9 / 6.6, 256x256 8.5 / 8.0 / 7.3; FP32 4.8 / - / 5.5, 6.0 / 5.4 / 5.6, 8.0 / 7.1
+// / 6.0).
 constexpr int MARCH_MIN_USE_PCT = 55;
-constexpr int TILE_FP32_MAX_SITES_PER_CU = 12 * 256;
+constexpr int TILE_FP32_MAX_SITES_PER_CU = 16 * 256;
+constexpr long long TILE_CACHE_BYTES = 256LL << 20;
 template <typename S>
 inline TwoStep choose_two_step(const Geo& g, int ncu, int max_lds, bool walls)
 {
@@ -591,14 +611,15 @@ inline TwoStep choose_two_step(const Geo& g, int ncu, int max_lds, bool walls)
     // LDS of either form: at most 154 KB; offsets of a site's populations in 32 bits
     constexpr int LDS = 157 * 1024;
     if (max_lds < LDS) return t;
+    const bool cached = 2 * g.total * (long long)sizeof(S) <= TILE_CACHE_BYTES;
     t.march = march_launch(g.lx, g.ly, MarchShape<S>::rows, 16, ncu, walls);
-    if (t.march.cost > 0 && (long long)NPOP * g.ps * (long long)sizeof(S) < (1LL << 31) &&
+    if (!cached && t.march.cost > 0 && (long long)NPOP * g.ps * (long long)sizeof(S) < (1LL << 31) &&
         sites * 100 >= (long long)MARCH_MIN_USE_PCT * t.march.cost * MarchShape<S>::rows * ncu) {
         t.kind = TWO_STEP_MARCH;
         return t;
     }
-    if (g.total * (long long)sizeof(S) >= (1LL << 32)) return t;
-    if (sizeof(S) == 4 && sites > (long long)TILE_FP32_MAX_SITES_PER_CU * ncu) return t;
+    if (g.total * (long long)sizeof(S) >= (1LL << 31)) return t;
+    if (sizeof(S) == 4 && !cached && sites > (long long)TILE_FP32_MAX_SITES_PER_CU * ncu) return t;
     auto tiles = [&](int tx, int ty) { return (long long)((g.lx + tx - 1) / tx) * ((g.ly + ty - 1) / ty); };
     if (tiles(8, 8) <= ncu) t.kind = TWO_STEP_TILE_8X8;
     else if (tiles(8, 16) <= ncu) t.kind = TWO_STEP_TILE_8X16;

@@ -22,10 +22,11 @@ def pops(lx, ly, precision, seed):
     return f if precision == "fp64" else (f - w).to(torch.float32)
 
 
-def check(lx, ly, n, precision, ybc, layout="columns"):
-    say(f"two steps per pass {lx}x{ly} n={n} {precision} {ybc} {layout}")
+def check(lx, ly, n, precision, ybc, layout="columns", xmode="wrap"):
+    say(f"two steps per pass {lx}x{ly} n={n} {precision} {ybc} {layout} {xmode}")
     f = pops(lx, ly, precision, 5)
-    a, b = (Lattice(lx, ly, TAU, G, TB, TT, precision=precision, ybc=ybc, step="fused", layout=layout, device=DEV)
+    a, b = (Lattice(lx, ly, TAU, G, TB, TT, precision=precision, ybc=ybc, step="fused", layout=layout, xmode=xmode,
+                    device=DEV)
             for _ in range(2))
     a.set_pops(f)
     b.set_pops(f)
@@ -36,7 +37,8 @@ def check(lx, ly, n, precision, ybc, layout="columns"):
     # the wall densities kept with the state, and those of the state before the
     # last step, which a further bc reads
     sa, sb = a.get_state(), b.get_state()
-    c = Lattice(lx, ly, TAU, G, TB, TT, precision=precision, ybc=ybc, step="fused", layout=layout, device=DEV)
+    c = Lattice(lx, ly, TAU, G, TB, TT, precision=precision, ybc=ybc, step="fused", layout=layout, xmode=xmode,
+                    device=DEV)
     c.set_state(sa)
     b.set_state(sb)
     c.step(1)
@@ -69,6 +71,15 @@ def test_tiles(lx, ly, ybc, precision):
 @pytest.mark.parametrize("precision", ["fp64", "fp32", "fp32_f32sums"])
 def test_march(lx, ly, ybc, precision):
     check(lx, ly, 5, precision, ybc, layout="planes" if lx == 901 else "columns")
+
+
+# x halos: passes of two steps wrap the index, single steps copy the halos; a
+# lattice for each of the forms
+@pytest.mark.parametrize("lx,ly", [(7, 7), (129, 257), (901, 1458)])
+@pytest.mark.parametrize("ybc", ["walls", "periodic"])
+@pytest.mark.parametrize("precision", ["fp64", "fp32"])
+def test_x_halos(lx, ly, ybc, precision):
+    check(lx, ly, 5, precision, ybc, xmode="halo")
 
 
 def test_march_largest():
