@@ -65,8 +65,7 @@ class RTRollout(torch.autograd.Function):
         dacc = torch.zeros((), dtype=torch.float64, device=P.device)
         ex = checkpoint.Executor(lat, dacc)
         ex.run(fwd)
-        ex.materialize()     # the lattice holds f_{N-1}
-        lat.step(1)          # f_N
+        ex.final_step()      # the lattice holds f_N
         T = lat.macros()[3]
         ctx.lat, ctx.ex, ctx.bwd, ctx.P, ctx.cfg = lat, ex, bwd, P, cfg
         cfg.stats.update(schedule_forward_steps=sch.forward_steps(), slots=sch.slots_needed,

@@ -17,7 +17,7 @@ LIB = os.path.join(HERE, "liblbm.so")
 # reference copy kernel used by the benchmark for roofline calibration
 PROBE_LIB = os.path.join(HERE, "libcopyprobe.so")
 SOURCES = ["lbm_api.hip"]
-HEADERS = ["lbm_site.hpp", "lbm_kernels.hpp", "lbm_twostep.hpp", "lbm_adjoint.hpp", "lbm_adjoint_api.inc", "lbm_layouts.hpp", "lbm_layouts_api.inc",
+HEADERS = ["lbm_site.hpp", "lbm_kernels.hpp", "lbm_twostep.hpp", "lbm_adjoint.hpp", "lbm_adjoint_api.inc", "lbm_layouts.hpp", "lbm_layouts_api.inc", "lbm_rollout.h",
            "lbm_hetero_api.inc", "host_band.h", "d2q37_tables.h"]
 # host-core part of co-execution: plain C++ with OpenMP, built by the host
 # compiler (AVX2 + FMA, so it runs on any x86-64-v3 host) and linked in

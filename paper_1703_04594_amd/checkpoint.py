@@ -224,12 +224,13 @@ class Executor:
     """Runs schedule actions against a Lattice (with adjoint buffers).
 
     The current forward state lives either in the lattice or in a slot.  A
-    restore only moves that marker; an advance by one step followed by a
-    store of the result is run as one step from the current slot straight
-    into the target slot (Lattice.step_state), so a replayed segment goes
-    from snapshot to snapshot without copying states in or out of the
-    lattice.  Results are bitwise those of the plain sequence (set_state,
-    step, get_state).  Reverse steps keep their d/dtau terms in the lattice
+    restore only moves that marker; an advance followed by a store of the
+    result runs from where the state is straight into the target slot, and an
+    advance on its own from a slot into the lattice (Lattice.advance_state; a
+    lattice without it chains single steps from slot to slot, step_state, and
+    copies otherwise), so no state is copied but one stored where it stands.
+    Results are bitwise those of the plain sequence (set_state, step,
+    get_state).  Reverse steps keep their d/dtau terms in the lattice
     (no reduction per step); run() adds them to dtau_acc before it returns."""
 
     LATTICE = -1
@@ -238,6 +239,7 @@ class Executor:
         self.lat = lat
         self.dtau = dtau_acc
         self.chain = chain
+        self.advance = getattr(lat, "advance_state", None) if chain else None
         self.pending_dtau = False
         self.slots: dict[int, object] = {}
         self.where = Executor.LATTICE
@@ -259,6 +261,16 @@ class Executor:
             self.state_copies += 1
             self.where = Executor.LATTICE
 
+    def final_step(self):
+        """Step the lattice on from the current forward state (the rollout's
+        last step, not counted in forward_steps)."""
+        if self.advance and self.where != Executor.LATTICE:
+            self.advance(self.slots[self.where], None, 1)
+            self.where = Executor.LATTICE
+        else:
+            self.materialize()
+            self.lat.step(1)
+
     def run(self, actions):
         i = 0
         while i < len(actions):
@@ -267,6 +279,17 @@ class Executor:
             if op == "advance":
                 a, b = act[1], act[2]
                 nxt = actions[i + 1] if i + 1 < len(actions) else None
+                if self.advance and b > a:
+                    src = None if self.where == Executor.LATTICE else self.slots[self.where]
+                    to = Executor.LATTICE
+                    if nxt is not None and nxt[0] == "store" and nxt[1] == b and nxt[2] != self.where:
+                        to = nxt[2]
+                        i += 1
+                    self.advance(src, None if to == Executor.LATTICE else self._slot(to), b - a)
+                    self.where = to
+                    self.forward_steps += b - a
+                    i += 1
+                    continue
                 if (self.chain and self.where != Executor.LATTICE and b - a == 1 and nxt is not None
                         and nxt[0] == "store" and nxt[1] == b and nxt[2] != self.where):
                     self.lat.step_state(self.slots[self.where], self._slot(nxt[2]))

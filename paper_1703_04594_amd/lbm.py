@@ -99,6 +99,7 @@ def lib() -> ctypes.CDLL:
     L.lbm_loss_temperature.argtypes = [vp, vp, vp]
     L.lbm_adjoint_step.argtypes = [vp, vp, vp]
     L.lbm_step_state.argtypes = [vp, vp, vp]
+    L.lbm_advance_state.argtypes = [vp, vp, vp, i64]
     L.lbm_adjoint_init_rt.argtypes = [vp, vp, ctypes.POINTER(RtProfileC), vp]
     L.lbm_last_error.argtypes = [vp]
     L.lbm_last_error.restype = ctypes.c_char_p
@@ -138,7 +139,7 @@ def lib() -> ctypes.CDLL:
     L.lbm_study_collide.restype = st
     for n in ("lbm_create", "lbm_set_tau", "lbm_init", "lbm_init_rt", "lbm_propagate", "lbm_bc",
               "lbm_collide", "lbm_step", "lbm_get_macros", "lbm_get_pops", "lbm_set_pops",
-              "lbm_get_state", "lbm_set_state", "lbm_step_state", "lbm_conservation", "lbm_loss_temperature",
+              "lbm_get_state", "lbm_set_state", "lbm_step_state", "lbm_advance_state", "lbm_conservation", "lbm_loss_temperature",
               "lbm_adjoint_seed_temperature", "lbm_adjoint_step", "lbm_adjoint_take_dtau", "lbm_adjoint_init_rt",
               "lbm_adjoint_get_lambda", "lbm_adjoint_set_lambda", "lbm_sync"):
         getattr(L, n).restype = st
@@ -305,6 +306,14 @@ class Lattice:
         ps = _ptr(src, torch.uint8, (self.state_bytes,), self.device)
         pd = _ptr(dst, torch.uint8, (self.state_bytes,), self.device)
         self._run("step_state", self.L.lbm_step_state, ctypes.c_void_p(ps), ctypes.c_void_p(pd))
+
+    def advance_state(self, src: torch.Tensor | None, dst: torch.Tensor | None, n: int):
+        """n steps from the snapshot src (None: the lattice's state) into the
+        snapshot dst (None: the lattice) without copies at either end
+        (lbm_advance_state); with dst the lattice's own state is not kept."""
+        ps, pd = (ctypes.c_void_p(_ptr(t, torch.uint8, (self.state_bytes,), self.device)) if t is not None else None
+                  for t in (src, dst))
+        self._run("advance_state", self.L.lbm_advance_state, ps, pd, int(n))
 
     def conservation(self) -> torch.Tensor:
         out = torch.empty(4, dtype=torch.float64, device=self.device)

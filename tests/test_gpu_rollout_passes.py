@@ -1,0 +1,61 @@
+"""A checkpointed rollout advances from snapshot to snapshot, several steps at
+a time.  Both sides evaluate the same expressions in the same order, so no
+tolerance applies."""
+import pytest
+import torch
+
+from paper_1703_04594_amd import inputs
+from paper_1703_04594_amd.lbm import Lattice
+
+from _util import G, TAU, TB, TT, say
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+def lattice(lx, ly, **kw):
+    lat = Lattice(lx, ly, TAU, G, TB, TT, device=DEV, **kw)
+    lat.init_rt(torch.tensor(inputs.rt_perturbation(lx, ly, 5), device=DEV))
+    return lat
+
+
+# a lattice of each form of the fused passes (tile, march) and the split step;
+# one and two passes, an odd step left over
+@pytest.mark.parametrize("lx,ly,kw", [
+    (40, 33, dict(precision="fp64", step="fused")), (129, 257, dict(precision="fp32", step="fused", ybc="periodic")),
+    (901, 1458, dict(precision="fp32", step="fused")), (64, 48, dict(precision="fp64", step="fused", xmode="halo")),
+    (64, 48, dict(precision="fp32", step="split"))])
+@pytest.mark.parametrize("n", [1, 2, 3, 4, 7])
+def test_advance_state_equals_single_steps(lx, ly, kw, n):
+    say(f"advance_state {lx}x{ly} n={n} {kw}")
+    a, b = lattice(lx, ly, **kw), lattice(lx, ly, **kw)
+    s0 = a.get_state()
+    chain = [s0]
+    for _ in range(n):
+        chain.append(b.new_state())
+        b.step_state(chain[-2], chain[-1])
+    b.set_state(chain[-1])
+    want = b.get_pops()
+    b.step(1)
+    after = b.get_pops()          # reads the wall densities kept with the state
+    out = a.new_state()
+
+    def holds(state):
+        if state is not None:
+            a.set_state(state)
+        assert torch.equal(a.get_pops(), want)
+        a.step(1)
+        assert torch.equal(a.get_pops(), after)
+
+    a.advance_state(s0, out, n)
+    holds(out)
+    a.advance_state(s0, None, n)
+    holds(None)
+    a.set_state(s0)
+    a.advance_state(None, out, n)
+    holds(out)
+    a.set_state(s0)
+    a.advance_state(None, None, n)
+    holds(None)
+    with pytest.raises(Exception):
+        a.advance_state(out, out, n)
