@@ -173,56 +173,92 @@ __device__ __forceinline__ void block_sum1(double v, double* __restrict__ partia
 // 8% (512x512) faster over FP32 states; with FP64 lambda they ran 1% slower.
 template <typename L>
 constexpr int adj_threads() { return sizeof(L) == 4 ? 64 : SITE_THREADS; }
+// With FP64 lambda too, small blocks on lattices that few_rows_fill names (us
+// per reverse step, FP64 / FP32 states: 211x333 17.6 / 15.6 with 256 threads,
+// 14.5 / 13.1 with 64; 301x1030 51.5 / 43.8 and 50.7 / 43.8; with nothing to
+// fill, 256x256 13.0 / 11.7 and 14.8 / 13.5).
+
+// WALL_HOP.of[l]: the hop of WH that population l (e_y != 0) is at its wall
+struct WallHopOf { int of[NPOP]; };
+constexpr WallHopOf make_wall_hop_of()
+{
+    WallHopOf t{};
+    for (int j = 0; j < NWS; ++j) t.of[WH.bot[j]] = t.of[WH.top[j]] = j;
+    return t;
+}
+constexpr WallHopOf WALL_HOP = make_wall_hop_of();
 
 // lambda_{n+1} at site (x, y) (see the header): from a buffer that holds mu
 // of the later step (GATHER), or lambda itself at each site (after a seed or
 // an explicit set).  Loads are unconditional: in the three rows next to a
 // wall the e_y-shifted ones reach into the ghost rows, and those values are
-// replaced by 0 below.
+// replaced by 0 in mend_lambda, with the mu of the wall slots that mirror onto
+// the site, which are read here: 15 loads in flight behind the others.
+template <typename L> struct WallMu { L mu[NWS]; };
 template <typename L, bool WALLS, bool GATHER>
-__device__ __forceinline__ void load_lambda(const L* __restrict__ buf, const Geo& lg, const WallTable& wt,
-                                            int x, int y, double (&lam)[NPOP])
+__device__ __forceinline__ void load_lambda(const L* __restrict__ buf, const Geo& lg, int x, int y, double (&lam)[NPOP],
+                                            WallMu<L>& wm)
 {
     const unsigned yd = (unsigned)y * (unsigned)sizeof(L);
-    if (!GATHER) {
-        const L* col = buf + lg.origin + (long long)x * lg.cs;
+    const L* col[7];   // columns x - 3 .. x + 3, at the running population
 #pragma unroll
-        for (int l = 0; l < NPOP; ++l) lam[l] = (double)ld_at(col + (size_t)l * lg.ps, yd);
-        return;
-    }
-    if (!WALLS) {
+    for (int k = 0; k < 7; ++k) col[k] = buf + lg.origin + (long long)(GATHER ? wrap_x(x + k - 3, lg.lx) : x) * lg.cs;
+    unsigned yp[7];    // byte offsets of rows y - 3 .. y + 3 of a lattice without walls
 #pragma unroll
-        for (int l = 0; l < NPOP; ++l) {
-            const int xs = wrap_x(x + EX[l], lg.lx);
-            int ys = y + EY[l];
-            ys = ys < 0 ? ys + lg.ly : (ys >= lg.ly ? ys - lg.ly : ys);
-            lam[l] = (double)buf[(size_t)l * lg.ps + lg.origin + (long long)xs * lg.cs + ys];
-        }
-        return;
-    }
+    for (int k = 0; k < 7; ++k) yp[k] = (unsigned)wrap_x(y + k - 3, lg.ly) * (unsigned)sizeof(L);
+    const int r = y < 3 ? y : lg.ly - 1 - y;   // rows from the wall
+    const bool near = WALLS && GATHER && r < 3;
+    long long lo = 0;
 #pragma unroll
     for (int l = 0; l < NPOP; ++l) {
-        const int xs = wrap_x(x + EX[l], lg.lx);
-        lam[l] = (double)ld_at(buf + (size_t)l * lg.ps + lg.origin + (long long)xs * lg.cs + EY[l], yd);
+        const L* p = col[GATHER ? 3 + EX[l] : 3] + lo;
+        if (!GATHER) lam[l] = (double)ld_at(p, yd);
+        else lam[l] = (double)(WALLS ? ld_at(p + EY[l], yd) : ld_at(p, yp[3 + EY[l]]));
+        lo += lg.ps;
+        asm volatile("" : "+s"(lo));   // one running offset, not 37 column addresses
     }
-    if (y < 3 || y >= lg.ly - 3) {
-        const int wall = y < 3 ? 0 : 1;
-        const int r = wall == 0 ? y : lg.ly - 1 - y;       // row counted from the wall
-        double beta = 0.0;
+    if (near) {
+        // the slot's row mirrors onto this one: en - 1 - r rows from the wall
+        if (y < 3) {
 #pragma unroll
-        for (int l = 0; l < NPOP; ++l) {
-            if (EY[l] == 0) continue;
-            const int en = wall == 0 ? EY[l] : -EY[l];      // hop component into the lattice
-            if (-en > r) lam[l] = 0.0;                      // s + e_l lies beyond the wall
-            if (en > r) {                                   // a wall slot that mirrors onto s
-                const int yw = wall == 0 ? en - 1 - r : lg.ly - en + r;
-                const int xw = wrap_x(x + EX[l], lg.lx);
-                beta += wt.ew[wall][l] * (double)buf[(size_t)l * lg.ps + lg.origin + (long long)xw * lg.cs + yw];
-            }
+            for (int j = 0; j < NWS; ++j)
+                wm.mu[j] = ld_at(col[3 + WH.ex[j]] + WH.bot[j] * lg.ps, (unsigned)max(WH.en[j] - 1 - r, 0) * (unsigned)sizeof(L));
+        } else {
+#pragma unroll
+            for (int j = 0; j < NWS; ++j)
+                wm.mu[j] = ld_at(col[3 + WH.ex[j]] + WH.top[j] * lg.ps,
+                                 (unsigned)(lg.ly - 1 - max(WH.en[j] - 1 - r, 0)) * (unsigned)sizeof(L));
         }
-#pragma unroll
-        for (int l = 0; l < NPOP; ++l) lam[l] += beta;
     }
+}
+// the wall W's part, r rows from it: populations from beyond the wall are 0,
+// and the wall slots that mirror onto the site act on its density
+template <typename L, int W>
+__device__ __forceinline__ void mend_lambda(double (&lam)[NPOP], int r, const WallTable& wt, const WallMu<L>& wm)
+{
+    double beta = 0.0;
+#pragma unroll
+    for (int l = 0; l < NPOP; ++l) {
+        if (EY[l] == 0) continue;
+        const int en = W == 0 ? EY[l] : -EY[l];      // hop component into the lattice
+        if (en < 0) {
+            lam[l] = -en > r ? 0.0 : lam[l];         // from beyond the wall
+        } else {
+            L mu = wm.mu[WALL_HOP.of[l]];
+            asm volatile("" : "+v"(mu));             // waited for and converted here
+            const double b = fma_(wt.ew[W][l], (double)mu, beta);
+            beta = en > r ? b : beta;
+        }
+    }
+#pragma unroll
+    for (int l = 0; l < NPOP; ++l) lam[l] += beta;
+}
+template <typename L, bool WALLS, bool GATHER>
+__device__ __forceinline__ void mend_lambda(double (&lam)[NPOP], int y, int ly, const WallTable& wt, const WallMu<L>& wm)
+{
+    if (!(WALLS && GATHER)) return;
+    if (y < 3) mend_lambda<L, 0>(lam, y, wt, wm);
+    else if (y >= ly - 3) mend_lambda<L, 1>(lam, ly - 1 - y, wt, wm);
 }
 
 // One reverse step at site (x, y): lambda_{n+1} (load_lambda), the gather
@@ -231,8 +267,17 @@ __device__ __forceinline__ void load_lambda(const L* __restrict__ buf, const Geo
 // partials (add: added to the slot, which then sums the terms of many steps).
 // (DEV: the device-scope streaming stores, or the plain non-temporal ones
 // below DEV_STORES_MIN_BLOCKS_PER_CU blocks per CU)
+//
+// HBM bounds it on large lattices (2048 x 4096, FP32 states: 5.9 TB/s with
+// FP64 lambda); below, the latency of its loads, of which 168 registers (three
+// waves per SIMD) hold both gathers.  The waves at a wall read the wall rule's
+// densities and mirrored mu together: as each was used, one latency each, they
+// held up the whole launch (us per step, before and after, with the column
+// addresses as one running offset: FP32 states and FP64 lambda 256x256 16.5 ->
+// 11.6, 512x512 44.3 -> 35.9, 1024x1024 184 -> 145; both FP64 512x512 48.5 -> 43.6,
+// 1024x2048 341 -> 334; both FP32 512x512 32.3 -> 26.5, 1024x2048 179 -> 170).
 template <typename S, typename L, bool WALLS, bool GATHER, int T = adj_threads<L>(), bool DEV = true>
-__global__ __launch_bounds__(T) void k_adj_collide(
+__global__ __launch_bounds__(T, 3) void k_adj_collide(
     const S* __restrict__ fn, Geo g, const L* __restrict__ lam_in, L* __restrict__ mu_out, Geo lg,
     AdjArgs a, const double* __restrict__ wall_rho, WallTable wt, double* __restrict__ partials, int add)
 {
@@ -244,51 +289,73 @@ __global__ __launch_bounds__(T) void k_adj_collide(
         const unsigned yb = (unsigned)y * (unsigned)sizeof(S);
         const unsigned yd = (unsigned)y * (unsigned)sizeof(L);
         double lam[NPOP];
-        load_lambda<L, WALLS, GATHER>(lam_in, lg, wt, x, y, lam);
+        WallMu<L> wm;
+        load_lambda<L, WALLS, GATHER>(lam_in, lg, x, y, lam, wm);
+        // FP64 states leave no registers for the wall's part beside both gathers
+        constexpr bool EARLY = sizeof(S) == 8;
+        if (EARLY) mend_lambda<L, WALLS, GATHER>(lam, y, g.ly, wt, wm);
         // the raw gather of f_n (storage precision; unconditional -- wall
         // slots read ghost rows and are replaced below)
+        const int r = y < 3 ? y : g.ly - 1 - y;   // rows from the wall
+        const bool near = WALLS && r < 3;
         Cc gl[NPOP];
+        {
+            const S* col[7];   // columns x - 3 .. x + 3, at the running population
 #pragma unroll
-        for (int l = 0; l < NPOP; ++l) {
-            int xs = wrap_x(x - EX[l], g.lx);
-            if (WALLS) {
-                gl[l] = (Cc)ld_at(fn + (size_t)l * g.ps + g.origin + (long long)xs * g.cs - EY[l], yb);
-            } else {
-                int ys = y - EY[l];
-                ys = ys < 0 ? ys + g.ly : (ys >= g.ly ? ys - g.ly : ys);
-                gl[l] = (Cc)fn[(size_t)l * g.ps + g.origin + (long long)xs * g.cs + ys];
+            for (int k = 0; k < 7; ++k) col[k] = fn + g.origin + (long long)wrap_x(x + k - 3, g.lx) * g.cs;
+            unsigned yp[7];    // byte offsets of rows y - 3 .. y + 3 of a lattice without walls
+#pragma unroll
+            for (int k = 0; k < 7; ++k) yp[k] = (unsigned)wrap_x(y + k - 3, g.ly) * (unsigned)sizeof(S);
+            long long lo = 0;
+#pragma unroll
+            for (int l = 0; l < NPOP; ++l) {
+                const S* p = col[3 - EX[l]] + lo;
+                gl[l] = (Cc)(WALLS ? ld_at(p - EY[l], yb) : ld_at(p, yp[3 - EY[l]]));
+                lo += g.ps;
+                asm volatile("" : "+s"(lo));
             }
         }
         // raw moments of g and Lg = sum_l lambda_l g_l, in FP64
         double m0 = 0.0, sx = 0.0, sy = 0.0, s2 = 0.0, Lg = 0.0;
-        if (WALLS && (y < 3 || y >= g.ly - 3)) {
+        auto add = [&](int l, double v) {
+            m0 += v;
+            if (EX[l] != 0) sx += (double)EX[l] * v;
+            if (EY[l] != 0) sy += (double)EY[l] * v;
+            if (R2_OF(l) != 0) s2 += (double)R2_OF(l) * v;
+            Lg += lam[l] * v;
+        };
+        auto raw = [&](int l) {
+            asm volatile("" : "+v"(gl[l]));   // converted where it is used, not for both branches ahead
+            return Store<S>::shifted ? (double)gl[l] + W_SHELL[SHELL[l]] : (double)gl[l];
+        };
+        if (near) {
+            if (!EARLY) mend_lambda<L, WALLS, GATHER>(lam, y, g.ly, wt, wm);
+            const int W = y < 3 ? 0 : 1;
+            const double* w0 = wall_rho + W * 3 * g.lx;
+            constexpr int CH = EARLY ? 13 : NPOP;   // populations whose densities are in flight together
 #pragma unroll
-            for (int l = 0; l < NPOP; ++l) {
-                double v = (double)gl[l];
-                if (Store<S>::shifted) v += W_SHELL[SHELL[l]];
-                if (EY[l] != 0) {
-                    const int wall = EY[l] > 0 ? 0 : 1;
-                    const int r = wall == 0 ? y : g.ly - 1 - y;
-                    const int en = wall == 0 ? EY[l] : -EY[l];
-                    if (en > r) v = wt.ew[wall][l] * wall_rho[(wall * 3 + (en - r - 1)) * g.lx + wrap_x(x - EX[l], g.lx)];
+            for (int c = 0; c < NPOP; c += CH) {
+                __builtin_amdgcn_sched_barrier(0);
+                double d[CH];
+#pragma unroll
+                for (int l = c; l < c + CH && l < NPOP; ++l)
+                    if (EY[l] != 0) {
+                        const int en = EY[l] > 0 ? EY[l] : -EY[l];
+                        d[l - c] = w0[max(en - 1 - r, 0) * g.lx + wrap_x(x - EX[l], g.lx)];
+                    }
+#pragma unroll
+                for (int l = c; l < c + CH && l < NPOP; ++l) {
+                    double v = raw(l);
+                    if (EY[l] != 0) {
+                        const int w = EY[l] > 0 ? 0 : 1, en = w == 0 ? EY[l] : -EY[l];
+                        v = W == w && en > r ? wt.ew[w][l] * d[l - c] : v;
+                    }
+                    add(l, v);
                 }
-                m0 += v;
-                if (EX[l] != 0) sx += (double)EX[l] * v;
-                if (EY[l] != 0) sy += (double)EY[l] * v;
-                if (R2_OF(l) != 0) s2 += (double)R2_OF(l) * v;
-                Lg += lam[l] * v;
             }
         } else {
 #pragma unroll
-            for (int l = 0; l < NPOP; ++l) {
-                double v = (double)gl[l];
-                if (Store<S>::shifted) v += W_SHELL[SHELL[l]];
-                m0 += v;
-                if (EX[l] != 0) sx += (double)EX[l] * v;
-                if (EY[l] != 0) sy += (double)EY[l] * v;
-                if (R2_OF(l) != 0) s2 += (double)R2_OF(l) * v;
-                Lg += lam[l] * v;
-            }
+            for (int l = 0; l < NPOP; ++l) add(l, raw(l));
         }
         dtau = adjoint_site(m0, sx, sy, s2, Lg, lam, a);
         L* mcol = mu_out + lg.origin + (long long)x * lg.cs;
@@ -342,7 +409,9 @@ __global__ __launch_bounds__(SITE_THREADS) void k_adj_init_rt(const L* __restric
     const double dr = -pr.p0 / (T0 * T0) * dT;
     const double th = T0 - 1.0;
     double lam[NPOP];
-    load_lambda<L, WALLS, GATHER>(lam_buf, lg, wt, x, y, lam);
+    WallMu<L> wm;
+    load_lambda<L, WALLS, GATHER>(lam_buf, lg, x, y, lam, wm);
+    mend_lambda<L, WALLS, GATHER>(lam, y, lg.ly, wt, wm);
     double acc = 0.0;
 #pragma unroll
     for (int l = 0; l < NPOP; ++l) {
@@ -363,7 +432,9 @@ __global__ __launch_bounds__(SITE_THREADS) void k_lambda_to_canon(const L* __res
     const int x = sb.x, y = sb.y;
     if (y >= lg.ly) return;
     double lam[NPOP];
-    load_lambda<L, WALLS, GATHER>(buf, lg, wt, x, y, lam);
+    WallMu<L> wm;
+    load_lambda<L, WALLS, GATHER>(buf, lg, x, y, lam, wm);
+    mend_lambda<L, WALLS, GATHER>(lam, y, lg.ly, wt, wm);
 #pragma unroll
     for (int l = 0; l < NPOP; ++l) canon[((size_t)l * lg.lx + x) * lg.ly + y] = lam[l];
 }

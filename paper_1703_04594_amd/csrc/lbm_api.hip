@@ -78,7 +78,8 @@ Plan plan(const lbm_params* p)
         pl.off_lam[1] = off; off += lb;
         // one partial per block of the reverse step (its blocks are the
         // smallest of the adjoint launches)
-        const int at = p->adjoint == 2 ? adj_threads<float>() : adj_threads<double>();
+        const int at = p->adjoint == 2 ? adj_threads<float>()
+                                       : (few_rows_fill(p->ly) ? SMALL_THREADS : adj_threads<double>());
         const size_t nb = (size_t)((p->ly + at - 1) / at) * p->lx;
         pl.off_apart = off; off += align_up(nb * 8, ALIGN);
         pl.off_adacc = off; off += align_up(nb * 8, ALIGN);
@@ -112,10 +113,11 @@ struct lbm_ctx {
     WallTable wt;
     CollideArgs cargs;
     unsigned fused_lds;  // dynamic LDS of the fused step's launch (occupancy cap; 0: none)
-    int fused_threads;   // threads per block of the FP64 fused step (256 or 512)
+    int fused_threads;   // threads per block of the FP64 fused step (64, 256 or 512)
     unsigned collide_lds;// the same for the split step's collide
     bool dev_stores;     // fused and reverse steps with device-scope stores (dev_stores_for)
     unsigned adj_lds;    // the same for the reverse step
+    bool adj_small;      // reverse step with FP64 lambda in 64-thread blocks
     TwoStep two;         // how lbm_step takes two steps in one pass (fused step, wrapped index)
     std::string err;
 
@@ -343,6 +345,8 @@ void launch_fused(lbm_ctx* c, const S* src, S* dst, const double* wr, double* wo
     } else {
         if (c->fused_threads == FUSED_FP64_WIDE_THREADS)
             launch_fused_kernel<S, true, FUSED_FP64_WIDE_THREADS>(c, src, dst, wr, wo);
+        else if (c->fused_threads == SMALL_THREADS)
+            launch_fused_kernel_dev<S, true, SMALL_THREADS, false>(c, src, dst, wr, wo);
         else
             launch_fused_kernel<S, true, SITE_THREADS>(c, src, dst, wr, wo);
     }
@@ -828,6 +832,7 @@ lbm_status lbm_create(const lbm_params* p, void* dev_workspace, size_t bytes, vo
         c->fused_threads = fl.threads;
         c->fused_lds = fl.lds;
         c->dev_stores = dev_stores_for(site_grid(pl.geo).x, ncu);
+        if (fl.lds == 0 && !c->dev_stores && few_rows_fill(p->ly)) c->fused_threads = SMALL_THREADS;
         if (p->step_kind == LBM_STEP_FUSED)
             c->two = p->precision == LBM_FP64 ? choose_two_step<double>(pl.geo, ncu, max_lds, p->ybc == LBM_Y_WALLS)
                                               : choose_two_step<float>(pl.geo, ncu, max_lds, p->ybc == LBM_Y_WALLS);
@@ -838,8 +843,9 @@ lbm_status lbm_create(const lbm_params* p, void* dev_workspace, size_t bytes, vo
         }
     }
     c->adj_lds = 0;
-    // (256-thread reverse steps only: FP64 lambda)
-    if (p->adjoint == 1 && ncu > 0 && (size_t)max_lds >= ADJ_LDS_RESERVE) {
+    c->adj_small = p->adjoint == 1 && !c->dev_stores && few_rows_fill(p->ly);
+    // (256-thread reverse steps only)
+    if (p->adjoint == 1 && !c->adj_small && ncu > 0 && (size_t)max_lds >= ADJ_LDS_RESERVE) {
         const int full = adj_blocks_per_cu(p, c->dev_stores);
         const size_t nb = site_grid(pl.geo).x;
         auto rounds = [&](int per_cu) { return (nb + (size_t)per_cu * ncu - 1) / ((size_t)per_cu * ncu); };

@@ -384,6 +384,44 @@ __device__ __forceinline__ void store_wall_density(const Cc (&f)[NPOP], const Ge
     }
 }
 
+// Wall slots of the three rows next to a wall, by hop (ex, en), en the
+// component into the lattice: the 15 populations with en > 0 at the bottom
+// wall, and their mirror images (ex, -en) at the top wall.
+constexpr int NWS = 15;
+struct WallHops { int bot[NWS], top[NWS], ex[NWS], en[NWS]; };
+constexpr WallHops make_wall_hops()
+{
+    WallHops t{};
+    int n = 0;
+    for (int l = 0; l < NPOP; ++l) {
+        if (EY[l] <= 0) continue;
+        t.bot[n] = l;
+        t.ex[n] = EX[l];
+        t.en[n] = EY[l];
+        for (int k = 0; k < NPOP; ++k)
+            if (EX[k] == EX[l] && EY[k] == -EY[l]) t.top[n] = k;
+        ++n;
+    }
+    return t;
+}
+constexpr WallHops WH = make_wall_hops();
+
+// The wall slots of a site r rows from wall W (r < 3), replaced in f by
+// f^eq_l(1, 0, T_wall) times the density rho(ex, k) of their mirror site, k
+// rows from the wall and ex columns back.  The densities are all read before
+// the first is used.
+template <typename S, int W, typename Cc>
+__device__ __forceinline__ void put_wall_slots(Cc (&f)[NPOP], int r, const WallTable& wt, const double (&d)[NWS])
+{
+#pragma unroll
+    for (int j = 0; j < NWS; ++j) {
+        const int l = W == 0 ? WH.bot[j] : WH.top[j];
+        double v = wt.ew[W][l] * d[j];
+        if (Store<S>::shifted) v -= W_SHELL[SHELL[l]];
+        f[l] = r < WH.en[j] ? (Cc)v : f[l];
+    }
+}
+
 // WIDE = false: FP32 storage collided with FP32 moment sums (collide_site).
 template <typename S, bool WALLS, bool WIDE = true>
 __global__ __launch_bounds__(SITE_THREADS) void k_collide(S* __restrict__ buf, Geo g, CollideArgs args,
@@ -420,6 +458,12 @@ __global__ __launch_bounds__(SITE_THREADS) void k_collide(S* __restrict__ buf, G
 // 2048x4096 and 4096x4096 and 1.2% at 2160x8192, but 3.5% slower at
 // 1024x2048 (same A/B, two runs each), so smaller lattices keep the
 // 256-thread form.
+// On small lattices its time is one wave's: the loads, the collision, the
+// stores.  In the waves at a wall the 15 densities of the wall rule are read
+// together, behind the populations (one at a time, as each slot was made, they
+// were the longest part; us per step, before and after: FP64 128x128 8.4 -> 5.8,
+// 256x256 11.0 -> 8.8, 1024x1024 119 -> 111; FP32 9.0 -> 6.5 at 256x128, 61.6 ->
+// 56.2 at 1024x1024; ahead of the populations 512x512 FP64 took 31.9, so 26.7).
 // ---------------------------------------------------------------------------
 constexpr unsigned FUSED_FP64_LDS_RESERVE = 64 * 1024;
 // the cap is applied from this many site blocks (of SITE_THREADS) per CU on
@@ -427,6 +471,19 @@ constexpr unsigned FUSED_FP64_CAP_MIN_BLOCKS_PER_CU = 16;
 constexpr int FUSED_FP64_WIDE_THREADS = 512;
 constexpr unsigned FUSED_FP64_WIDE_LDS_RESERVE = 96 * 1024;
 constexpr unsigned FUSED_FP64_WIDE_MIN_BLOCKS_PER_CU = 64;
+
+// Where 256-thread blocks would leave more than an eighth of the rows' number
+// of lanes idle that 64-thread ones fill, the FP64 step runs those as long as
+// it takes no cap (us per step: 211x333 13.0 with 256 threads, 9.1 with 64,
+// 301x1030 39.7 and 33.4; with nothing to fill, 512x512 26.6 and 28.1, 1000x1501
+// 158 and 182).  The FP32 step does not gain (211x333 8.3 and 9.5).
+constexpr int SMALL_THREADS = 64;
+inline bool few_rows_fill(int ly)
+{
+    const int big = (ly + SITE_THREADS - 1) / SITE_THREADS * SITE_THREADS;
+    const int small = (ly + SMALL_THREADS - 1) / SMALL_THREADS * SMALL_THREADS;
+    return (big - small) * 8LL > ly;
+}
 
 // Launch settings of the FP64 fused step (and of its access-pattern probe)
 // for a lattice of nb256 blocks of SITE_THREADS sites on a GPU of ncu CUs
@@ -458,7 +515,7 @@ constexpr unsigned COLLIDE_FP32_LDS_RESERVE = 64 * 1024;
 // registers) takes a reserve that leaves 2 blocks per CU only when that does
 // not add a round of blocks: rounds = ceil(blocks / (blocks per CU x CUs)).
 // That holds on small lattices alone (up to 4 blocks per CU), e.g. 512x512,
-// where it runs 12% faster; wherever the cap adds a round it cost 3-60%
+// where it runs 8% faster (FP32 states 35.9 us against 39.2); wherever the cap adds a round it cost 3-60%
 // (sweep from 256x256 to 2048x4096).  With FP32 lambda the reverse step runs
 // 64-thread blocks and no cap.
 constexpr unsigned ADJ_LDS_RESERVE = 64 * 1024;
@@ -478,41 +535,42 @@ __global__ __launch_bounds__(T) void k_step_fused(const S* __restrict__ src, S* 
     unsigned yp[7];   // byte offsets of rows y - 3 .. y + 3 of a lattice without walls
 #pragma unroll
     for (int k = 0; k < 7; ++k) yp[k] = (unsigned)wrap_x(y + k - 3, g.ly) * (unsigned)sizeof(S);
+    const int r = y < 3 ? y : g.ly - 1 - y;   // rows from the wall
+    const bool near = WALLS && r < 3;
     Cc f[NPOP];
     // FP64: the 37 gathers are issued at raised wave priority, so a wave that
     // reaches them is not held behind other waves' collide arithmetic
     // (measured 0.4% on the 2048x4096 step; results are unchanged).
     if constexpr (sizeof(S) == 8) __builtin_amdgcn_s_setprio(3);
+    const S* col[7];   // columns x - 3 .. x + 3, at the running population
+#pragma unroll
+    for (int k = 0; k < 7; ++k) col[k] = src + g.origin + (long long)(WRAP ? wrap_x(x + k - 3, g.lx) : x + k - 3) * g.cs;
+    long long lo = 0;
 #pragma unroll
     for (int l = 0; l < NPOP; ++l) {
-        int xs = x - EX[l];
-        if (WRAP) xs = wrap_x(xs, g.lx);
-        const S* col = src + (size_t)l * g.ps + g.origin + (long long)xs * g.cs;
-        f[l] = (Cc)(WALLS ? ld_at(col - EY[l], yb) : ld_at(col, yp[3 - EY[l]]));
+        const S* p = col[3 - EX[l]] + lo;
+        f[l] = (Cc)(WALLS ? ld_at(p - EY[l], yb) : ld_at(p, yp[3 - EY[l]]));
+        lo += g.ps;
+        asm volatile("" : "+s"(lo));   // one running offset, not 37 column addresses
+    }
+    double d[NWS];
+    if (near) {   // all in flight together, behind the populations
+        const double* w0 = wall_rho + (y < 3 ? 0 : 3 * g.lx);
+#pragma unroll
+        for (int j = 0; j < NWS; ++j) d[j] = w0[max(WH.en[j] - 1 - r, 0) * g.lx + wrap_x(x - WH.ex[j], g.lx)];
     }
     if constexpr (sizeof(S) == 8) {
         __builtin_amdgcn_sched_barrier(0);
         __builtin_amdgcn_s_setprio(0);
     }
-    if (WALLS && (y < 3 || y >= g.ly - 3)) {
-#pragma unroll
-        for (int l = 0; l < NPOP; ++l) {
-            if (EY[l] == 0) continue;
-            const int wall = EY[l] > 0 ? 0 : 1;
-            const int r = wall == 0 ? y : g.ly - 1 - y;       // row counted from the wall
-            const int en = wall == 0 ? EY[l] : -EY[l];
-            if (en > r) {
-                const int xs = wrap_x(x - EX[l], g.lx);
-                double v = wt.ew[wall][l] * wall_rho[(wall * 3 + (en - r - 1)) * g.lx + xs];
-                if (Store<S>::shifted) v -= W_SHELL[SHELL[l]];
-                f[l] = (Cc)v;
-            }
-        }
+    if (near) {
+        if (y < 3) put_wall_slots<S, 0>(f, r, wt, d);
+        else put_wall_slots<S, 1>(f, r, wt, d);
     }
     collide_site<Cc, Store<S>::shifted, WIDE>(f, args);
-    S* col = dst + g.origin + (long long)x * g.cs;
+    S* out = dst + g.origin + (long long)x * g.cs;
 #pragma unroll
-    for (int l = 0; l < NPOP; ++l) st_stream<DEV>(col + (size_t)l * g.ps, yb, (S)f[l]);
+    for (int l = 0; l < NPOP; ++l) st_stream<DEV>(out + (size_t)l * g.ps, yb, (S)f[l]);
     if (WALLS) store_wall_density<S>(f, g, x, y, wall_rho_out);
 }
 

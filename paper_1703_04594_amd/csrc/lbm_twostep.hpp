@@ -44,44 +44,6 @@ constexpr int ex_rank(int l)
     return n;
 }
 
-// Wall slots of the three rows next to a wall, by hop (ex, en), en the
-// component into the lattice: the 15 populations with en > 0 at the bottom
-// wall, and their mirror images (ex, -en) at the top wall.
-constexpr int NWS = 15;
-struct WallHops { int bot[NWS], top[NWS], ex[NWS], en[NWS]; };
-constexpr WallHops make_wall_hops()
-{
-    WallHops t{};
-    int n = 0;
-    for (int l = 0; l < NPOP; ++l) {
-        if (EY[l] <= 0) continue;
-        t.bot[n] = l;
-        t.ex[n] = EX[l];
-        t.en[n] = EY[l];
-        for (int k = 0; k < NPOP; ++k)
-            if (EX[k] == EX[l] && EY[k] == -EY[l]) t.top[n] = k;
-        ++n;
-    }
-    return t;
-}
-constexpr WallHops WH = make_wall_hops();
-
-// The wall slots of a site r rows from wall W (r < 3), replaced in f by
-// f^eq_l(1, 0, T_wall) times the density rho(ex, k) of their mirror site, k
-// rows from the wall and ex columns back.  The densities are all read before
-// the first is used.
-template <typename S, int W, typename Cc>
-__device__ __forceinline__ void put_wall_slots(Cc (&f)[NPOP], int r, const WallTable& wt, const double (&d)[NWS])
-{
-#pragma unroll
-    for (int j = 0; j < NWS; ++j) {
-        const int l = W == 0 ? WH.bot[j] : WH.top[j];
-        double v = wt.ew[W][l] * d[j];
-        if (Store<S>::shifted) v -= W_SHELL[SHELL[l]];
-        f[l] = r < WH.en[j] ? (Cc)v : f[l];
-    }
-}
-
 // Buffer accesses: block-uniform base, per-lane and uniform 32-bit byte offsets.
 template <typename S>
 __device__ __forceinline__ S buf_load(__amdgpu_buffer_rsrc_t r, int voff, int soff)
