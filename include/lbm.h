@@ -127,8 +127,9 @@ size_t lbm_state_bytes(const lbm_params* p);
  * LBM_ERR_SIZE if bytes is too small) and binds
  * a context to dev_workspace (>= lbm_workspace_bytes(p) bytes, 256-byte
  * aligned, caller-owned, must outlive the context) and hip_stream (a
- * hipStream_t, or NULL for the default stream).  Zeroes the workspace.  The
- * context holds host-side metadata only. */
+ * hipStream_t, or NULL for the default stream).  Zeroes the workspace but for
+ * the adjoint state, on that stream and without waiting for it; LBM_ERR_HIP
+ * while the stream is captured.  The context holds host-side metadata only. */
 lbm_status lbm_create(const lbm_params* p, void* dev_workspace, size_t bytes,
                       void* hip_stream, lbm_ctx** out);
 /* Frees the host-side context; never touches the workspace. NULL is a no-op. */

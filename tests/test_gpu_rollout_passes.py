@@ -5,7 +5,7 @@ import pytest
 import torch
 
 from paper_1703_04594_amd import inputs
-from paper_1703_04594_amd.lbm import Lattice
+from paper_1703_04594_amd.lbm import Lattice, LBMError
 
 from _util import G, TAU, TB, TT, say
 
@@ -59,3 +59,43 @@ def test_advance_state_equals_single_steps(lx, ly, kw, n):
     holds(None)
     with pytest.raises(Exception):
         a.advance_state(out, out, n)
+
+
+@pytest.mark.parametrize("lam", ["fp64", "fp32"])
+@pytest.mark.parametrize("ybc", ["walls", "periodic"])
+@pytest.mark.parametrize("precision", ["fp64", "fp32"])
+def test_reverse_steps_do_not_depend_on_the_workspace_they_get(precision, ybc, lam):
+    """A context does not clear its adjoint state: reverse steps in a workspace
+    that held NaN equal those in one that held zeros."""
+    lx, ly = 40, 33
+    say(f"workspace contents {precision} {ybc} {lam}")
+    gT = torch.tensor(inputs.uniform_field(lx, ly, 4, -1, 1), device=DEV)
+    out = []
+    for fill in (0.0, float("nan")):
+        nbytes = lattice(lx, ly, precision=precision, ybc=ybc, step="fused", adjoint=lam).workspace.numel()
+        torch.full((nbytes // 8 + 32,), fill, dtype=torch.float64, device=DEV)   # freed: the next one's memory
+        lat = lattice(lx, ly, precision=precision, ybc=ybc, step="fused", adjoint=lam)
+        states = [lat.get_state()]
+        lat.step(1)
+        states.append(lat.get_state())
+        lat.seed_temperature(gT)
+        dtau = torch.zeros((), dtype=torch.float64, device=DEV)
+        for s in reversed(states):
+            lat.adjoint_step(s, dtau)
+        out.append((lat.get_lambda(), dtau))
+    assert torch.isfinite(out[1][0]).all()
+    assert torch.equal(out[0][0], out[1][0]) and torch.equal(out[0][1], out[1][1])
+
+
+def test_a_context_is_not_created_in_a_capture():
+    lattice(40, 33, precision="fp64")     # the library is loaded
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    t = torch.zeros(8, device=DEV)
+    with torch.cuda.graph(g):
+        t += 1
+        with pytest.raises(LBMError):
+            Lattice(40, 33, TAU, G, TB, TT, device=DEV)
+    g.replay()
+    torch.cuda.synchronize()
+    assert torch.equal(t, torch.ones_like(t))
