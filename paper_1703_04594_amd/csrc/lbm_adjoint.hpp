@@ -265,8 +265,6 @@ __device__ __forceinline__ void mend_lambda(double (&lam)[NPOP], int y, int ly, 
 // g = bc(propagate(f_n)) of the snapshot f_n, collide^T, and mu stored at the
 // site (aligned streaming stores); the block's d/dtau term goes to its slot of
 // partials (add: added to the slot, which then sums the terms of many steps).
-// (DEV: the device-scope streaming stores, or the plain non-temporal ones
-// below DEV_STORES_MIN_BLOCKS_PER_CU blocks per CU)
 //
 // HBM bounds it on large lattices (2048 x 4096, FP32 states: 5.9 TB/s with
 // FP64 lambda); below, the latency of its loads, of which 168 registers (three
@@ -276,7 +274,7 @@ __device__ __forceinline__ void mend_lambda(double (&lam)[NPOP], int y, int ly, 
 // addresses as one running offset: FP32 states and FP64 lambda 256x256 16.5 ->
 // 11.6, 512x512 44.3 -> 35.9, 1024x1024 184 -> 145; both FP64 512x512 48.5 -> 43.6,
 // 1024x2048 341 -> 334; both FP32 512x512 32.3 -> 26.5, 1024x2048 179 -> 170).
-template <typename S, typename L, bool WALLS, bool GATHER, int T = adj_threads<L>(), bool DEV = true>
+template <typename S, typename L, bool WALLS, bool GATHER, int T = adj_threads<L>(), StoreKind ST = STORE_DEV>
 __global__ __launch_bounds__(T, 3) void k_adj_collide(
     const S* __restrict__ fn, Geo g, const L* __restrict__ lam_in, L* __restrict__ mu_out, Geo lg,
     AdjArgs a, const double* __restrict__ wall_rho, WallTable wt, double* __restrict__ partials, int add)
@@ -360,7 +358,7 @@ __global__ __launch_bounds__(T, 3) void k_adj_collide(
         dtau = adjoint_site(m0, sx, sy, s2, Lg, lam, a);
         L* mcol = mu_out + lg.origin + (long long)x * lg.cs;
 #pragma unroll
-        for (int l = 0; l < NPOP; ++l) st_stream<DEV>(mcol + (size_t)l * lg.ps, yd, (L)lam[l]);
+        for (int l = 0; l < NPOP; ++l) st_stream<ST>(mcol + (size_t)l * lg.ps, yd, (L)lam[l]);
     }
     block_sum1<T>(dtau, partials, add != 0);
 }

@@ -116,7 +116,7 @@ struct lbm_ctx {
     int fused_threads;   // threads per block of the FP64 fused step (64, 256 or 512)
     unsigned collide_lds;// the same for the split step's collide
     bool dev_stores;     // fused and reverse steps with device-scope stores (dev_stores_for)
-    unsigned adj_lds;    // the same for the reverse step
+    StoreKind adj_stores; // kind of the reverse step's stores
     bool adj_small;      // reverse step with FP64 lambda in 64-thread blocks
     TwoStep two;         // how lbm_step takes two steps in one pass (fused step, wrapped index)
     std::string err;
@@ -304,9 +304,9 @@ lbm_status do_collide(lbm_ctx* c)
 }
 
 // One fused step src -> dst (wall densities read from wr, written to wo),
-// T threads per block.
-template <typename S, bool WIDE, int T, bool DEV>
-void launch_fused_kernel_dev(lbm_ctx* c, const S* src, S* dst, const double* wr, double* wo)
+// T threads per block, stores of kind ST.
+template <typename S, bool WIDE, int T, StoreKind ST>
+void launch_fused_kernel(lbm_ctx* c, const S* src, S* dst, const double* wr, double* wo)
 {
     const Geo& g = c->pl.geo;
     const bool walls = c->p.ybc == LBM_Y_WALLS;
@@ -314,42 +314,41 @@ void launch_fused_kernel_dev(lbm_ctx* c, const S* src, S* dst, const double* wr,
     const unsigned lds = sizeof(S) == 8 ? c->fused_lds : 0u;
     const dim3 grid((unsigned)((g.ly + T - 1) / T) * (unsigned)g.lx);
     if (wrap && walls)
-        hipLaunchKernelGGL((k_step_fused<S, true, true, WIDE, T, DEV>), grid, dim3(T), lds, c->stream, src, dst, g,
+        hipLaunchKernelGGL((k_step_fused<S, true, true, WIDE, T, ST>), grid, dim3(T), lds, c->stream, src, dst, g,
                            c->cargs, wr, c->wt, wo);
     else if (wrap)
-        hipLaunchKernelGGL((k_step_fused<S, true, false, WIDE, T, DEV>), grid, dim3(T), lds, c->stream, src, dst, g,
+        hipLaunchKernelGGL((k_step_fused<S, true, false, WIDE, T, ST>), grid, dim3(T), lds, c->stream, src, dst, g,
                            c->cargs, wr, c->wt, wo);
     else if (walls)
-        hipLaunchKernelGGL((k_step_fused<S, false, true, WIDE, T, DEV>), grid, dim3(T), lds, c->stream, src, dst, g,
+        hipLaunchKernelGGL((k_step_fused<S, false, true, WIDE, T, ST>), grid, dim3(T), lds, c->stream, src, dst, g,
                            c->cargs, wr, c->wt, wo);
     else
-        hipLaunchKernelGGL((k_step_fused<S, false, false, WIDE, T, DEV>), grid, dim3(T), lds, c->stream, src, dst, g,
+        hipLaunchKernelGGL((k_step_fused<S, false, false, WIDE, T, ST>), grid, dim3(T), lds, c->stream, src, dst, g,
                            c->cargs, wr, c->wt, wo);
 }
-template <typename S, bool WIDE, int T>
-void launch_fused_kernel(lbm_ctx* c, const S* src, S* dst, const double* wr, double* wo)
-{
-    if (c->dev_stores) launch_fused_kernel_dev<S, WIDE, T, true>(c, src, dst, wr, wo);
-    else launch_fused_kernel_dev<S, WIDE, T, false>(c, src, dst, wr, wo);
-}
 
+// buffers: population buffers that a run of such steps goes through
 template <typename S>
-void launch_fused(lbm_ctx* c, const S* src, S* dst, const double* wr, double* wo)
+void launch_fused(lbm_ctx* c, const S* src, S* dst, const double* wr, double* wo, int buffers)
 {
+    const StoreKind st = store_kind_for(c->dev_stores, (size_t)buffers * c->pl.buf_bytes, STEP_CACHED_MIN_BYTES);
+#define FUSED(WIDE, T)                                                                              \
+    (st == STORE_CACHED ? launch_fused_kernel<S, WIDE, T, STORE_CACHED>(c, src, dst, wr, wo)         \
+     : st == STORE_NT   ? launch_fused_kernel<S, WIDE, T, STORE_NT>(c, src, dst, wr, wo)             \
+                        : launch_fused_kernel<S, WIDE, T, STORE_DEV>(c, src, dst, wr, wo))
     if constexpr (std::is_same<S, float>::value) {
-        if (c->f32_sums()) {
-            launch_fused_kernel<S, false, SITE_THREADS>(c, src, dst, wr, wo);
-            return;
-        }
-        launch_fused_kernel<S, true, SITE_THREADS>(c, src, dst, wr, wo);
+        if (c->f32_sums()) FUSED(false, SITE_THREADS);
+        else FUSED(true, SITE_THREADS);
+    } else if (c->fused_threads == FUSED_FP64_WIDE_THREADS) {   // beyond the caches
+        if (st == STORE_DEV) launch_fused_kernel<S, true, FUSED_FP64_WIDE_THREADS, STORE_DEV>(c, src, dst, wr, wo);
+        else launch_fused_kernel<S, true, FUSED_FP64_WIDE_THREADS, STORE_NT>(c, src, dst, wr, wo);
+    } else if (c->fused_threads == SMALL_THREADS) {             // below device-scope stores
+        if (st == STORE_CACHED) launch_fused_kernel<S, true, SMALL_THREADS, STORE_CACHED>(c, src, dst, wr, wo);
+        else launch_fused_kernel<S, true, SMALL_THREADS, STORE_NT>(c, src, dst, wr, wo);
     } else {
-        if (c->fused_threads == FUSED_FP64_WIDE_THREADS)
-            launch_fused_kernel<S, true, FUSED_FP64_WIDE_THREADS>(c, src, dst, wr, wo);
-        else if (c->fused_threads == SMALL_THREADS)
-            launch_fused_kernel_dev<S, true, SMALL_THREADS, false>(c, src, dst, wr, wo);
-        else
-            launch_fused_kernel<S, true, SITE_THREADS>(c, src, dst, wr, wo);
+        FUSED(true, SITE_THREADS);
     }
+#undef FUSED
 }
 
 template <typename S>
@@ -364,7 +363,7 @@ lbm_status do_step_fused(lbm_ctx* c)
         s = ensure_wall_density<S>(c, c->cur);
         if (s) return s;
     }
-    launch_fused<S>(c, src, dst, c->wall_rho(c->wr_cur), c->wall_rho(1 - c->wr_cur));
+    launch_fused<S>(c, src, dst, c->wall_rho(c->wr_cur), c->wall_rho(1 - c->wr_cur), 2);
     s = check_launch(c, "step_fused");
     if (s) return s;
     c->cur = 1 - c->cur;
@@ -600,6 +599,12 @@ lbm_status do_get_state(lbm_ctx* c, char* dst)
                       "get_state");
 }
 
+// A chain of steps through snapshots goes through more buffers than two: counted
+// as four for the kind of its stores (us per step of a chain through four,
+// non-temporal / cached: FP32 512x512 15.8 / 14.2, 768x768 33.1 / 35.2, FP64 512x512
+// 26.2 / 27.9).
+constexpr int CHAIN_BUFFERS = 4;
+
 // One fused step from snapshot src into snapshot dst (both buffer + wall
 // densities); the context's own buffers and wall tables are not touched.
 template <typename S>
@@ -612,7 +617,7 @@ lbm_status do_step_state(lbm_ctx* c, char* src, char* dst)
     const bool walls = c->p.ybc == LBM_Y_WALLS;
     const double* wr = walls ? (const double*)(src + c->pl.buf_bytes) : nullptr;
     double* wo = walls ? (double*)(dst + c->pl.buf_bytes) : nullptr;
-    launch_fused<S>(c, sb, db, wr, wo);
+    launch_fused<S>(c, sb, db, wr, wo, CHAIN_BUFFERS);
     return check_launch(c, "step_state");
 }
 
@@ -643,7 +648,7 @@ lbm_status do_advance_state(lbm_ctx* c, char* src, char* dst, int64_t n)
         } else {
             s = launch_pre_stream<S>(c, sb, false);
             if (s) return s;
-            launch_fused<S>(c, sb, db, wr, wo);
+            launch_fused<S>(c, sb, db, wr, wo, src || dst ? CHAIN_BUFFERS : 2);
             s = check_launch(c, "advance_state");
         }
         if (s) return s;
@@ -754,32 +759,6 @@ lbm_status launch_conservation_noalloc(const Geo& g, const void* pops, double* p
 
 }  // namespace
 
-namespace {
-
-// Blocks of the reverse step's kernel that fit one CU at full occupancy
-// (0 if the runtime cannot tell).
-template <typename S, typename L>
-int adj_blocks_per_cu_t(bool dev_stores)
-{
-    int n = 0;
-    constexpr int T = adj_threads<L>();
-    const hipError_t e =
-        dev_stores ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_adj_collide<S, L, true, true, T, true>, T, 0)
-                   : hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_adj_collide<S, L, true, true, T, false>, T, 0);
-    return e == hipSuccess ? n : 0;
-}
-
-// blocks per CU of the reverse step this context launches
-int adj_blocks_per_cu(const lbm_params* p, bool dev_stores)
-{
-    const bool lam32 = p->adjoint == 2;
-    if (p->precision == LBM_FP64)
-        return lam32 ? adj_blocks_per_cu_t<double, float>(dev_stores) : adj_blocks_per_cu_t<double, double>(dev_stores);
-    return lam32 ? adj_blocks_per_cu_t<float, float>(dev_stores) : adj_blocks_per_cu_t<float, double>(dev_stores);
-}
-
-}  // namespace
-
 // ============================================================================
 // C ABI
 // ============================================================================
@@ -842,16 +821,8 @@ lbm_status lbm_create(const lbm_params* p, void* dev_workspace, size_t bytes, vo
                 c->collide_lds = coll;
         }
     }
-    c->adj_lds = 0;
+    c->adj_stores = store_kind_for(c->dev_stores, pl.buf_bytes + 2 * (pl.off_lam[1] - pl.off_lam[0]), ADJ_CACHED_MIN_BYTES);
     c->adj_small = p->adjoint == 1 && !c->dev_stores && few_rows_fill(p->ly);
-    // (256-thread reverse steps only)
-    if (p->adjoint == 1 && !c->adj_small && ncu > 0 && (size_t)max_lds >= ADJ_LDS_RESERVE) {
-        const int full = adj_blocks_per_cu(p, c->dev_stores);
-        const size_t nb = site_grid(pl.geo).x;
-        auto rounds = [&](int per_cu) { return (nb + (size_t)per_cu * ncu - 1) / ((size_t)per_cu * ncu); };
-        if (full > ADJ_CAP_BLOCKS_PER_CU && rounds(ADJ_CAP_BLOCKS_PER_CU) <= rounds(full))
-            c->adj_lds = ADJ_LDS_RESERVE;
-    }
     // Everything but the adjoint state, whose sites a seed or a set writes first
     // and whose padding no result depends on (512 x 512 with FP64 lambda: 78 of
     // 234 MB, 16 us of 48).  In stream order; a context cannot be created in a

@@ -189,14 +189,14 @@ __device__ __forceinline__ void st_nt(T* base, unsigned byte_off, T v)
         __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4_t, v), r, (int)byte_off, 0,
                                                STORE_CPOL_NT_SC1);
 }
-// The fused step's and reverse step's stores: the device-scope streaming
-// store above (DEV), or the plain non-temporal store, which their
-// instantiations for lattices below DEV_STORES_MIN_BLOCKS_PER_CU blocks per CU
-// use.
-template <bool DEV, typename T>
+// The fused step's and reverse step's stores: cached ones, non-temporal ones,
+// or the device-scope streaming store above (store_kind_for).
+enum StoreKind { STORE_CACHED, STORE_NT, STORE_DEV };
+template <StoreKind ST, typename T>
 __device__ __forceinline__ void st_stream(T* base, unsigned byte_off, T v)
 {
-    if constexpr (DEV) st_nt(base, byte_off, v);
+    if constexpr (ST == STORE_DEV) st_nt(base, byte_off, v);
+    else if constexpr (ST == STORE_CACHED) *reinterpret_cast<T*>(reinterpret_cast<char*>(base) + byte_off) = v;
     else __builtin_nontemporal_store(v, reinterpret_cast<T*>(reinterpret_cast<char*>(base) + byte_off));
 }
 // Device scope pays on large lattices only (see st_nt): the fused and reverse
@@ -211,6 +211,24 @@ constexpr unsigned DEV_STORES_MIN_BLOCKS_PER_CU = 128;
 inline bool dev_stores_for(size_t nb256, int ncu)
 {
     return ncu > 0 && nb256 >= (size_t)DEV_STORES_MIN_BLOCKS_PER_CU * (size_t)ncu;
+}
+// Cached stores pay where the working set of a step (its buffers, the reverse
+// step's two lambda buffers and state) is more than the L2s hold and fits the
+// Infinity Cache, from which the next step then reads.  us per step,
+// non-temporal / cached (working set in MB): FP64 step 256x256 (44) 8.8 / 9.2,
+// 384x384 (92) 16.6 / 14.1, 512x512 (162) 27.1 / 23.4, 640x640 (251) 47 / 36,
+// 768x768 (359) 65.3 / 65.3, 1024x1024 111 / 120; FP32 step 211x333 (22) 8.4 / 9.5,
+// 512x512 (81) 16.5 / 14.3, 768x768 (180) 33.7 / 29.6; reverse step over FP32
+// states, FP64 lambda 300x300 (75) 14.3 / 15.8, 384x384 (115) 23.0 / 20.4, 512x512
+// (203) 36.5 / 33.7, 301x1030 (237) 44.2 / 38.3, 768x768 (449) 76 / 90; both FP64
+// 300x300 (90) 15.9 / 16.9, 512x512 (243) 43.3 / 39.4; both FP32 384x384 (69) 16.8 /
+// 17.7, 512x512 (122) 26.6 / 25.8, 768x768 (270) 46.6 / 49.0.
+constexpr size_t CACHED_STORES_MAX_BYTES = 256u << 20;
+constexpr size_t STEP_CACHED_MIN_BYTES = 64u << 20, ADJ_CACHED_MIN_BYTES = 96u << 20;
+inline StoreKind store_kind_for(bool dev_stores, size_t working_set, size_t cached_min)
+{
+    if (dev_stores) return STORE_DEV;
+    return working_set >= cached_min && working_set <= CACHED_STORES_MAX_BYTES ? STORE_CACHED : STORE_NT;
 }
 template <typename T>
 __device__ __forceinline__ void st_at(T* base, unsigned byte_off, T v)
@@ -511,18 +529,7 @@ inline FusedLaunch fused_fp64_launch(size_t nb256, int ncu, int max_lds)
 // slower at 2048x4096 and 4096x4096.
 constexpr unsigned COLLIDE_FP64_LDS_RESERVE = 64 * 1024;
 constexpr unsigned COLLIDE_FP32_LDS_RESERVE = 64 * 1024;
-// The reverse step with FP64 lambda (256-thread blocks, 3 per CU by its
-// registers) takes a reserve that leaves 2 blocks per CU only when that does
-// not add a round of blocks: rounds = ceil(blocks / (blocks per CU x CUs)).
-// That holds on small lattices alone (up to 4 blocks per CU), e.g. 512x512,
-// where it runs 8% faster (FP32 states 35.9 us against 39.2); wherever the cap adds a round it cost 3-60%
-// (sweep from 256x256 to 2048x4096).  With FP32 lambda the reverse step runs
-// 64-thread blocks and no cap.
-constexpr unsigned ADJ_LDS_RESERVE = 64 * 1024;
-constexpr int ADJ_CAP_BLOCKS_PER_CU = 2;
-// DEV: the device-scope streaming stores (large lattices) or the plain
-// non-temporal ones (below DEV_STORES_MIN_BLOCKS_PER_CU blocks per CU)
-template <typename S, bool WRAP, bool WALLS, bool WIDE = true, int T = SITE_THREADS, bool DEV = true>
+template <typename S, bool WRAP, bool WALLS, bool WIDE = true, int T = SITE_THREADS, StoreKind ST = STORE_DEV>
 __global__ __launch_bounds__(T) void k_step_fused(const S* __restrict__ src, S* __restrict__ dst, Geo g,
                                                   CollideArgs args, const double* __restrict__ wall_rho, WallTable wt,
                                                   double* __restrict__ wall_rho_out)
@@ -570,7 +577,7 @@ __global__ __launch_bounds__(T) void k_step_fused(const S* __restrict__ src, S* 
     collide_site<Cc, Store<S>::shifted, WIDE>(f, args);
     S* out = dst + g.origin + (long long)x * g.cs;
 #pragma unroll
-    for (int l = 0; l < NPOP; ++l) st_stream<DEV>(out + (size_t)l * g.ps, yb, (S)f[l]);
+    for (int l = 0; l < NPOP; ++l) st_stream<ST>(out + (size_t)l * g.ps, yb, (S)f[l]);
     if (WALLS) store_wall_density<S>(f, g, x, y, wall_rho_out);
 }
 
