@@ -167,8 +167,8 @@ void set_collide_args(lbm_ctx* c)
 // 1-D grid of site blocks, renumbered per XCD inside the kernels (site_block)
 dim3 site_grid(const Geo& g) { return dim3((unsigned)((g.ly + SITE_THREADS - 1) / SITE_THREADS) * (unsigned)g.lx); }
 
-template <typename S>
-lbm_status launch_propagate(lbm_ctx* c, const S* src, S* dst)
+template <typename S, bool CACHED>
+lbm_status launch_propagate_kind(lbm_ctx* c, const S* src, S* dst)
 {
     const Geo& g = c->pl.geo;
     constexpr int VEC = sizeof(S) == 8 ? 2 : 4;
@@ -183,14 +183,29 @@ lbm_status launch_propagate(lbm_ctx* c, const S* src, S* dst)
     const bool wrap = c->p.xmode == LBM_X_WRAP;
     const unsigned nb = (unsigned)nblk;
     if (wrap && cols)
-        hipLaunchKernelGGL((k_propagate<S, VEC, UNROLL, true, true>), grid, dim3(PROP_THREADS), 0, c->stream, src, dst, g, nb);
+        hipLaunchKernelGGL((k_propagate<S, VEC, UNROLL, true, true, CACHED>), grid, dim3(PROP_THREADS), 0, c->stream, src, dst, g,
+                           nb);
     else if (wrap)
-        hipLaunchKernelGGL((k_propagate<S, VEC, UNROLL, true, false>), grid, dim3(PROP_THREADS), 0, c->stream, src, dst, g, nb);
+        hipLaunchKernelGGL((k_propagate<S, VEC, UNROLL, true, false, CACHED>), grid, dim3(PROP_THREADS), 0, c->stream, src, dst, g,
+                           nb);
     else if (cols)
-        hipLaunchKernelGGL((k_propagate<S, VEC, UNROLL, false, true>), grid, dim3(PROP_THREADS), 0, c->stream, src, dst, g, nb);
+        hipLaunchKernelGGL((k_propagate<S, VEC, UNROLL, false, true, CACHED>), grid, dim3(PROP_THREADS), 0, c->stream, src, dst, g,
+                           nb);
     else
-        hipLaunchKernelGGL((k_propagate<S, VEC, UNROLL, false, false>), grid, dim3(PROP_THREADS), 0, c->stream, src, dst, g, nb);
+        hipLaunchKernelGGL((k_propagate<S, VEC, UNROLL, false, false, CACHED>), grid, dim3(PROP_THREADS), 0, c->stream, src, dst, g,
+                           nb);
     return check_launch(c, "propagate");
+}
+// the split step's kernels with cached loads and stores
+bool split_cached(const lbm_ctx* c)
+{
+    const size_t both = 2 * c->pl.buf_bytes;
+    return both >= SPLIT_CACHED_MIN_BYTES && both <= CACHED_STORES_MAX_BYTES;
+}
+template <typename S>
+lbm_status launch_propagate(lbm_ctx* c, const S* src, S* dst)
+{
+    return split_cached(c) ? launch_propagate_kind<S, true>(c, src, dst) : launch_propagate_kind<S, false>(c, src, dst);
 }
 
 template <typename S>
@@ -273,19 +288,27 @@ lbm_status do_bc(lbm_ctx* c)
 
 // In-place collide of the current buffer; wo receives the wall densities
 // (WALLS) -- FP32 storage with FP32 sums takes the WIDE = false kernels.
+template <typename S, bool WALLS, bool WIDE>
+void launch_collide_wide(lbm_ctx* c, double* wo)
+{
+    const Geo& g = c->pl.geo;
+    if (split_cached(c))
+        hipLaunchKernelGGL((k_collide<S, WALLS, WIDE, true>), site_grid(g), dim3(SITE_THREADS), 0, c->stream,
+                           (S*)c->buf(c->cur), g, c->cargs, wo);
+    else
+        hipLaunchKernelGGL((k_collide<S, WALLS, WIDE, false>), site_grid(g), dim3(SITE_THREADS), c->collide_lds, c->stream,
+                           (S*)c->buf(c->cur), g, c->cargs, wo);
+}
 template <typename S, bool WALLS>
 void launch_collide(lbm_ctx* c, double* wo)
 {
-    const Geo& g = c->pl.geo;
     if constexpr (std::is_same<S, float>::value) {
         if (c->f32_sums()) {
-            hipLaunchKernelGGL((k_collide<S, WALLS, false>), site_grid(g), dim3(SITE_THREADS), c->collide_lds,
-                               c->stream, (S*)c->buf(c->cur), g, c->cargs, wo);
+            launch_collide_wide<S, WALLS, false>(c, wo);
             return;
         }
     }
-    hipLaunchKernelGGL((k_collide<S, WALLS, true>), site_grid(g), dim3(SITE_THREADS), c->collide_lds, c->stream,
-                       (S*)c->buf(c->cur), g, c->cargs, wo);
+    launch_collide_wide<S, WALLS, true>(c, wo);
 }
 
 template <typename S>

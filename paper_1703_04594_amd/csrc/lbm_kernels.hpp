@@ -262,6 +262,12 @@ template <> struct VecA<float, 4> { typedef float T __attribute__((ext_vector_ty
 // region of memory together).  Measured on the 2048x4096 lattice, this beat
 // 1, 2, 8 and 16 KB workgroups, temporal loads, an XCD-contiguous
 // renumbering and a 3-D (chunk, population, column) grid.
+// CACHED: plain loads and stores, where the two buffers of a split step fit the
+// Infinity Cache and are more than the L2s hold (us per propagate, non-temporal /
+// cached, FP64 and FP32: 256x256 9.4 / 8.8 and 6.7 / 8.0, 300x333 11.9 / 11.0 and
+// 8.8 / 9.4, 512x512 26.1 / 23.6 and 14.7 / 13.7, 768x768 63.5 / 69.8 and 29.2 /
+// 26.5, 1080x4096 400 / 491 and 200 / 222).
+constexpr size_t SPLIT_CACHED_MIN_BYTES = 40u << 20;
 constexpr int PROP_THREADS = 256;
 constexpr int PROP_UNROLL = 1;
 // widest x dimension of the propagate grid in workgroups: a dispatch holds
@@ -270,7 +276,7 @@ constexpr int PROP_UNROLL = 1;
 // slower than one row at 2048x8192.
 constexpr unsigned PROP_GRID_X = 0xffffffffu / PROP_THREADS;
 
-template <typename S, int VEC, int UNROLL, bool WRAP, bool COLS>
+template <typename S, int VEC, int UNROLL, bool WRAP, bool COLS, bool CACHED>
 __global__ __launch_bounds__(PROP_THREADS) void k_propagate(const S* __restrict__ src, S* __restrict__ dst, Geo g,
                                                             unsigned nblk)
 {
@@ -293,12 +299,17 @@ __global__ __launch_bounds__(PROP_THREADS) void k_propagate(const S* __restrict_
 #pragma unroll
     for (int u = 0; u < UNROLL; ++u) {
         const int y = y0 + u * PROP_THREADS * VEC;
-        if (y < g.ly) v[u] = __builtin_nontemporal_load(reinterpret_cast<const VU*>(sp + y));
+        if (y < g.ly) {
+            const VU* p = reinterpret_cast<const VU*>(sp + y);
+            v[u] = CACHED ? *p : __builtin_nontemporal_load(p);
+        }
     }
 #pragma unroll
     for (int u = 0; u < UNROLL; ++u) {
         const int y = y0 + u * PROP_THREADS * VEC;
-        if (y < g.ly) st_nt<VA>(reinterpret_cast<VA*>(dp), (unsigned)y * (unsigned)sizeof(S), (VA)v[u]);
+        if (y >= g.ly) continue;
+        if (CACHED) *reinterpret_cast<VA*>(dp + y) = (VA)v[u];
+        else st_nt<VA>(reinterpret_cast<VA*>(dp), (unsigned)y * (unsigned)sizeof(S), (VA)v[u]);
     }
 }
 
@@ -441,7 +452,11 @@ __device__ __forceinline__ void put_wall_slots(Cc (&f)[NPOP], int r, const WallT
 }
 
 // WIDE = false: FP32 storage collided with FP32 moment sums (collide_site).
-template <typename S, bool WALLS, bool WIDE = true>
+// CACHED: plain loads and stores, where propagate takes them (us per collide,
+// non-temporal / cached, FP64 and FP32: 256x256 8.9 / 7.4 and 6.5 / 6.3, 512x512 30.8 /
+// 24.4 and 16.7 / 14.0, 640x640 48.3 / 36.8 and 27 / 22.7, 1080x4096 408 / 467 and 208 /
+// 242; behind a non-temporal propagate, FP32 256x256 took 17 us per step against 16).
+template <typename S, bool WALLS, bool WIDE = true, bool CACHED = false>
 __global__ __launch_bounds__(SITE_THREADS) void k_collide(S* __restrict__ buf, Geo g, CollideArgs args,
                                                        double* __restrict__ wall_rho_out)
 {
@@ -453,10 +468,10 @@ __global__ __launch_bounds__(SITE_THREADS) void k_collide(S* __restrict__ buf, G
     const unsigned yb = (unsigned)y * (unsigned)sizeof(S);
     Cc f[NPOP];
 #pragma unroll
-    for (int l = 0; l < NPOP; ++l) f[l] = (Cc)ld_nt(col + (size_t)l * g.ps, yb);
+    for (int l = 0; l < NPOP; ++l) f[l] = (Cc)(CACHED ? ld_at(col + (size_t)l * g.ps, yb) : ld_nt(col + (size_t)l * g.ps, yb));
     collide_site<Cc, Store<S>::shifted, WIDE>(f, args);
 #pragma unroll
-    for (int l = 0; l < NPOP; ++l) st_nt(col + (size_t)l * g.ps, yb, (S)f[l]);
+    for (int l = 0; l < NPOP; ++l) st_stream<CACHED ? STORE_CACHED : STORE_DEV>(col + (size_t)l * g.ps, yb, (S)f[l]);
     if (WALLS) store_wall_density<S>(f, g, x, y, wall_rho_out);
 }
 

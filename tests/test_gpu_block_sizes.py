@@ -45,3 +45,22 @@ def test_steps_match_the_oracle(ly, ybc):
     e_t = abs(float(dtau) - float(tau.grad)) / abs(float(tau.grad))
     say(f"  f {e_f:.2e}  lambda {e_l:.2e}  dtau {e_t:.2e}")
     assert e_f <= 1e-13 and e_l <= 1e-12 and e_t <= 1e-12
+
+
+# working sets (two buffers) below, inside and beyond the range that takes cached
+# loads and stores: bitwise the fused step, which evaluates the same expressions
+@pytest.mark.parametrize("lx,ly", [(200, 250), (301, 333), (512, 400), (1000, 900)])
+@pytest.mark.parametrize("precision", ["fp64", "fp32"])
+@pytest.mark.parametrize("ybc,layout,xmode", [("walls", "columns", "wrap"), ("periodic", "planes", "halo")])
+def test_split_steps_equal_fused_ones(lx, ly, precision, ybc, layout, xmode):
+    say(f"split and fused {lx}x{ly} {precision} {ybc} {layout} {xmode}")
+    P = torch.tensor(inputs.rt_perturbation(lx, ly, 7), device=DEV)
+    out = []
+    for step in ("split", "fused"):
+        lat = Lattice(lx, ly, TAU, -1e-3, TB, TT, precision=precision, ybc=ybc, layout=layout, xmode=xmode, step=step,
+                      device=DEV)
+        lat.init_rt(P)
+        for _ in range(3):
+            lat.step(1)
+        out.append(lat.get_pops())
+    assert torch.equal(out[0], out[1])
