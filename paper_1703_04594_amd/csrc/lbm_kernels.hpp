@@ -439,8 +439,8 @@ constexpr WallHops WH = make_wall_hops();
 // f^eq_l(1, 0, T_wall) times the density rho(ex, k) of their mirror site, k
 // rows from the wall and ex columns back.  The densities are all read before
 // the first is used.
-template <typename S, int W, typename Cc>
-__device__ __forceinline__ void put_wall_slots(Cc (&f)[NPOP], int r, const WallTable& wt, const double (&d)[NWS])
+template <typename S, int W, typename Cc, typename Wt>
+__device__ __forceinline__ void put_wall_slots(Cc (&f)[NPOP], int r, const Wt& wt, const double (&d)[NWS])
 {
 #pragma unroll
     for (int j = 0; j < NWS; ++j) {

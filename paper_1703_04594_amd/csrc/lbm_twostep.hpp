@@ -69,9 +69,9 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t buf_of(S* base)
 // Without walls the gather wraps the row as it does the column, so a pass needs
 // no ghost rows (512 x 512: 2.6-3.6 us per pass for the launch that filled them).
 // What bounds a pass: on the smallest lattices the chain of one load, two
-// collisions and an LDS exchange (256 x 128 FP64: 11.7 us per two steps against
-// 17 us in single steps); above, the first step's work on the rings (512 x 512:
-// 33.5 us against 55 us FP64, 28 against 36 us FP32).
+// collisions and an LDS exchange (256 x 128 FP64: 10.5 us per two steps against
+// 13 us in single steps, without walls 9.2); above, the first step's work on the
+// rings (512 x 512: 33 us against 47 us FP64, 27.6 against 28.5 us FP32).
 // The buffer accesses keep one SGPR offset running over the populations: with
 // 64-bit column addresses 512 x 512 FP64 took 40.3 us, FP32 31.1.  The wall
 // densities are read ahead of the populations (behind them 128 x 128 FP64
@@ -82,6 +82,24 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t buf_of(S* base)
 // ---------------------------------------------------------------------------
 template <int TX, int TY>
 constexpr int tile_threads() { return ((TX + 6) * (TY + 6) + 63) / 64 * 64; }
+
+// The tile kernel's wall table, read from its argument segment where it is
+// used: as a plain argument the compiler loads it on entry, in several rounds of
+// scalar loads ahead of the gather, and spills it (us per step, before and
+// after: FP64 128x128 4.8 -> 4.4, 256x128 5.9 -> 5.3, 256x256 7.3 -> 6.6, FP32 384x384
+// 10.9 -> 10.1; the single step and the reverse step, which had fewer rounds, gain
+// nothing).  TileArgs mirrors the segment: the kernel's parameters in order.
+template <typename S>
+struct TileArgs { const S* src; S* dst; Geo g; CollideArgs args; const double* wall_rho; WallTable wt; };
+typedef const __attribute__((address_space(4))) char* kernarg_t;
+typedef const __attribute__((address_space(4))) WallTable wall_table_arg_t;
+template <typename S>
+__device__ __forceinline__ wall_table_arg_t& tile_wall_table()
+{
+    kernarg_t p = (kernarg_t)__builtin_amdgcn_kernarg_segment_ptr() + offsetof(TileArgs<S>, wt);
+    asm volatile("" : "+s"(p));   // not loaded ahead of this point
+    return *(wall_table_arg_t*)p;
+}
 
 template <typename S, bool WALLS, bool WIDE, int TX, int TY>
 __global__ __launch_bounds__((tile_threads<TX, TY>()), WIDE ? 4 : 6) void k_twostep_tile(
@@ -132,8 +150,9 @@ __global__ __launch_bounds__((tile_threads<TX, TY>()), WIDE ? 4 : 6) void k_twos
                 soff += stride;
             }
             if (near) {
-                if (y < 3) put_wall_slots<S, 0>(f, r, wt, d);
-                else put_wall_slots<S, 1>(f, r, wt, d);
+                auto& w = tile_wall_table<S>();
+                if (y < 3) put_wall_slots<S, 0>(f, r, w, d);
+                else put_wall_slots<S, 1>(f, r, w, d);
             }
             collide_site<Cc, Store<S>::shifted, WIDE>(f, args);
             const int ox = ax - 3, oy = ay - 3;
@@ -165,8 +184,9 @@ __global__ __launch_bounds__((tile_threads<TX, TY>()), WIDE ? 4 : 6) void k_twos
                 double d[NWS];
 #pragma unroll
                 for (int j = 0; j < NWS; ++j) d[j] = wr[WALLS ? w0 + max(WH.en[j] - 1 - r, 0) : 0][ox + 3 - WH.ex[j]];
-                if (y < 3) put_wall_slots<S, 0>(f, r, wt, d);
-                else put_wall_slots<S, 1>(f, r, wt, d);
+                auto& w = tile_wall_table<S>();
+                if (y < 3) put_wall_slots<S, 0>(f, r, w, d);
+                else put_wall_slots<S, 1>(f, r, w, d);
             }
             const __amdgpu_buffer_rsrc_t rs = buf_of(dst + g.origin);
             const int off = (X * (int)g.cs + y) * (int)sizeof(S);
@@ -559,7 +579,7 @@ struct TwoStep { TwoStepKind kind; MarchLaunch march; };
 // per CU (1024x1024: 115 against 123; 2048x4096: 957 against 862).
 // The smallest tiles are taken while they leave no CU with more than one
 // (us per step, 8x8 / 8x16 / 16x16: FP64 128x128 4.7 / - / 6.2, 256x128 6.3 /
-// 5.9 / 6.6, 256x256 8.5 / 8.0 / 7.3; FP32 4.8 / - / 5.5, 6.0 / 5.4 / 5.6, 8.0 / 7.1
+// 5.9 / 6.6, 256x256 8.5 / 8.0 / 7.3 before the wall table was read late; FP32 4.8 / - / 5.5, 6.0 / 5.4 / 5.6, 8.0 / 7.1
 // / 6.0).
 constexpr int MARCH_MIN_USE_PCT = 55;
 constexpr int TILE_FP32_MAX_SITES_PER_CU = 16 * 256;
