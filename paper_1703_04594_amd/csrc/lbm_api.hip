@@ -647,10 +647,13 @@ lbm_status do_step_state(lbm_ctx* c, char* src, char* dst)
 // n fused steps (n >= 1) from snapshot src, or the current state if NULL, into
 // snapshot dst, or the current state if NULL: the first pass reads src and the
 // last writes dst, so a snapshot at either end costs no copy (1024 x 2048 FP32:
-// 110 us each).  The passes between use the context's buffers.
+// 110 us each).  The passes between use the context's buffers, and passes of two
+// steps its table WALL_MID, so lbm_bc is refused until a state precedes the
+// current one again.
 template <typename S>
 lbm_status do_advance_state(lbm_ctx* c, char* src, char* dst, int64_t n)
 {
+    c->have_prev = false;
     const bool walls = c->p.ybc == LBM_Y_WALLS;
     S* sb = src ? (S*)src : (S*)c->buf(c->cur);
     const double* wr = src ? (const double*)(src + c->pl.buf_bytes) : c->wall_rho(c->wr_cur);
@@ -680,8 +683,6 @@ lbm_status do_advance_state(lbm_ctx* c, char* src, char* dst, int64_t n)
         c->cur = b;
         c->wr_cur = w;
         c->wr_buf = walls ? b : -1;
-        c->have_prev = false;
-        c->prev_mid = false;
         sb = db;
         wr = wo;
     }
