@@ -168,7 +168,8 @@ lbm_status lbm_collide(lbm_ctx* ctx);
  * into a HIP graph there (after at least one eager step).  A replay repeats
  * the captured launches with the buffers they were captured with: capture an
  * even n, which ends on the buffers it started from, and each replay then
- * advances the state by n steps, bitwise as n eager steps would. */
+ * advances the state by n steps, bitwise as n eager steps would; lbm_bc after
+ * it is the one after those steps. */
 lbm_status lbm_step(lbm_ctx* ctx, int64_t n);
 
 /* ---- read-out and snapshots ---------------------------------------------- */

@@ -32,7 +32,7 @@ struct Plan {
     size_t wall_bytes;// one wall-density table (6 * lx doubles)
     size_t state_bytes; // snapshot: population buffer + its wall densities
     size_t off_buf[2];
-    size_t off_wall;  // 3 x 6 * lx doubles (double-buffered wall densities, and those of the state in between)
+    size_t off_wall;  // 3 x 6 * lx doubles (double-buffered wall densities, and those of the state in between), and a word
     size_t off_part;  // RED_BLOCKS * 4 doubles, then 2 doubles of loss/dtau scratch
     size_t off_lam[2];
     size_t off_apart; // adjoint: one double per collide block
@@ -70,7 +70,7 @@ Plan plan(const lbm_params* p)
     size_t off = 0;
     pl.off_buf[0] = off; off += pl.buf_bytes;
     pl.off_buf[1] = off; off += pl.buf_bytes;
-    pl.off_wall = off; off += 3 * pl.wall_bytes;
+    pl.off_wall = off; off += 3 * pl.wall_bytes + ALIGN;
     pl.off_part = off; off += align_up(((size_t)RED_BLOCKS * 4 + 2) * 8, ALIGN);
     if (p->adjoint) {
         const size_t lb = align_up((size_t)pl.lgeo.total * (p->adjoint == 2 ? 4 : 8), ALIGN);
@@ -98,8 +98,10 @@ struct lbm_ctx {
     char* ws;
     hipStream_t stream;
     int cur;           // current population buffer
-    bool have_prev;    // the other buffer holds the state before the last propagate
-    bool prev_mid;     // ... except that the last pass took two steps: that state's wall densities are in table WALL_MID
+    // the other buffer holds the state before the last propagate, except after a
+    // pass of two steps: that state's wall densities are in table WALL_MID then
+    // (set_mid_word)
+    bool have_prev;
     int lam_cur;
     bool have_lambda;
     // lambda buffer lam_cur holds mu of the last reverse step (lambda is its
@@ -124,6 +126,10 @@ struct lbm_ctx {
     void* buf(int i) { return ws + pl.off_buf[i]; }
     double* wall_rho(int i) { return reinterpret_cast<double*>(ws + pl.off_wall + i * pl.wall_bytes); }
     static constexpr int WALL_MID = 2;
+    // the table of the states in between, and the word behind it; NULL where no
+    // pass takes two steps or there are no walls
+    double* wall_mid() { return two.kind != TWO_STEP_NONE && p.ybc == LBM_Y_WALLS ? wall_rho(WALL_MID) : nullptr; }
+    double* mid_word() { return wall_mid() ? wall_mid() + 6 * (size_t)p.lx : nullptr; }
     double* partials() { return reinterpret_cast<double*>(ws + pl.off_part); }
     double* scratch2() { return partials() + (size_t)RED_BLOCKS * 4; }
     template <typename L> L* lam(int i) { return reinterpret_cast<L*>(ws + pl.off_lam[i]); }
@@ -184,16 +190,16 @@ lbm_status launch_propagate_kind(lbm_ctx* c, const S* src, S* dst)
     const unsigned nb = (unsigned)nblk;
     if (wrap && cols)
         hipLaunchKernelGGL((k_propagate<S, VEC, UNROLL, true, true, CACHED>), grid, dim3(PROP_THREADS), 0, c->stream, src, dst, g,
-                           nb);
+                           nb, c->mid_word());
     else if (wrap)
         hipLaunchKernelGGL((k_propagate<S, VEC, UNROLL, true, false, CACHED>), grid, dim3(PROP_THREADS), 0, c->stream, src, dst, g,
-                           nb);
+                           nb, c->mid_word());
     else if (cols)
         hipLaunchKernelGGL((k_propagate<S, VEC, UNROLL, false, true, CACHED>), grid, dim3(PROP_THREADS), 0, c->stream, src, dst, g,
-                           nb);
+                           nb, c->mid_word());
     else
         hipLaunchKernelGGL((k_propagate<S, VEC, UNROLL, false, false, CACHED>), grid, dim3(PROP_THREADS), 0, c->stream, src, dst, g,
-                           nb);
+                           nb, c->mid_word());
     return check_launch(c, "propagate");
 }
 // the split step's kernels with cached loads and stores
@@ -262,7 +268,6 @@ lbm_status do_propagate(lbm_ctx* c)
     if (c->wr_buf == 1 - c->cur) c->wr_buf = -1;   // destination overwritten
     c->cur = 1 - c->cur;
     c->have_prev = true;
-    c->prev_mid = false;
     return LBM_OK;
 }
 
@@ -272,17 +277,10 @@ lbm_status do_bc(lbm_ctx* c)
     if (c->p.ybc == LBM_Y_PERIODIC) return LBM_OK;
     if (!c->have_prev) return fail(c, LBM_ERR_STATE, "bc: no propagate since the state was set");
     const Geo& g = c->pl.geo;
-    const double* wr = nullptr;
-    if (c->prev_mid) {
-        wr = c->wall_rho(lbm_ctx::WALL_MID);
-        c->wr_buf = -1;   // the current buffer's wall rows change
-    } else {
-        lbm_status s = ensure_wall_density<S>(c, 1 - c->cur);
-        if (s) return s;
-        wr = c->wall_rho(c->wr_cur);
-    }
+    lbm_status s = ensure_wall_density<S>(c, 1 - c->cur);
+    if (s) return s;
     hipLaunchKernelGGL((k_bc_apply<S>), dim3((NSLOT * g.lx + 255) / 256), dim3(256), 0, c->stream,
-                       (S*)c->buf(c->cur), g, wr, c->wt);
+                       (S*)c->buf(c->cur), g, (const double*)c->wall_rho(c->wr_cur), (const double*)c->wall_mid(), c->wt);
     return check_launch(c, "bc_apply");
 }
 
@@ -329,7 +327,7 @@ lbm_status do_collide(lbm_ctx* c)
 // One fused step src -> dst (wall densities read from wr, written to wo),
 // T threads per block, stores of kind ST.
 template <typename S, bool WIDE, int T, StoreKind ST>
-void launch_fused_kernel(lbm_ctx* c, const S* src, S* dst, const double* wr, double* wo)
+void launch_fused_kernel(lbm_ctx* c, const S* src, S* dst, const double* wr, double* wo, double* mid_word)
 {
     const Geo& g = c->pl.geo;
     const bool walls = c->p.ybc == LBM_Y_WALLS;
@@ -338,36 +336,37 @@ void launch_fused_kernel(lbm_ctx* c, const S* src, S* dst, const double* wr, dou
     const dim3 grid((unsigned)((g.ly + T - 1) / T) * (unsigned)g.lx);
     if (wrap && walls)
         hipLaunchKernelGGL((k_step_fused<S, true, true, WIDE, T, ST>), grid, dim3(T), lds, c->stream, src, dst, g,
-                           c->cargs, wr, c->wt, wo);
+                           c->cargs, wr, c->wt, wo, mid_word);
     else if (wrap)
         hipLaunchKernelGGL((k_step_fused<S, true, false, WIDE, T, ST>), grid, dim3(T), lds, c->stream, src, dst, g,
-                           c->cargs, wr, c->wt, wo);
+                           c->cargs, wr, c->wt, wo, mid_word);
     else if (walls)
         hipLaunchKernelGGL((k_step_fused<S, false, true, WIDE, T, ST>), grid, dim3(T), lds, c->stream, src, dst, g,
-                           c->cargs, wr, c->wt, wo);
+                           c->cargs, wr, c->wt, wo, mid_word);
     else
         hipLaunchKernelGGL((k_step_fused<S, false, false, WIDE, T, ST>), grid, dim3(T), lds, c->stream, src, dst, g,
-                           c->cargs, wr, c->wt, wo);
+                           c->cargs, wr, c->wt, wo, mid_word);
 }
 
-// buffers: population buffers that a run of such steps goes through
+// buffers: population buffers that a run of such steps goes through; mid_word:
+// NULL for a step between snapshots
 template <typename S>
-void launch_fused(lbm_ctx* c, const S* src, S* dst, const double* wr, double* wo, int buffers)
+void launch_fused(lbm_ctx* c, const S* src, S* dst, const double* wr, double* wo, int buffers, double* mid_word)
 {
     const StoreKind st = store_kind_for(c->dev_stores, (size_t)buffers * c->pl.buf_bytes, STEP_CACHED_MIN_BYTES);
 #define FUSED(WIDE, T)                                                                              \
-    (st == STORE_CACHED ? launch_fused_kernel<S, WIDE, T, STORE_CACHED>(c, src, dst, wr, wo)         \
-     : st == STORE_NT   ? launch_fused_kernel<S, WIDE, T, STORE_NT>(c, src, dst, wr, wo)             \
-                        : launch_fused_kernel<S, WIDE, T, STORE_DEV>(c, src, dst, wr, wo))
+    (st == STORE_CACHED ? launch_fused_kernel<S, WIDE, T, STORE_CACHED>(c, src, dst, wr, wo, mid_word) \
+     : st == STORE_NT   ? launch_fused_kernel<S, WIDE, T, STORE_NT>(c, src, dst, wr, wo, mid_word)   \
+                        : launch_fused_kernel<S, WIDE, T, STORE_DEV>(c, src, dst, wr, wo, mid_word))
     if constexpr (std::is_same<S, float>::value) {
         if (c->f32_sums()) FUSED(false, SITE_THREADS);
         else FUSED(true, SITE_THREADS);
     } else if (c->fused_threads == FUSED_FP64_WIDE_THREADS) {   // beyond the caches
-        if (st == STORE_DEV) launch_fused_kernel<S, true, FUSED_FP64_WIDE_THREADS, STORE_DEV>(c, src, dst, wr, wo);
-        else launch_fused_kernel<S, true, FUSED_FP64_WIDE_THREADS, STORE_NT>(c, src, dst, wr, wo);
+        if (st == STORE_DEV) launch_fused_kernel<S, true, FUSED_FP64_WIDE_THREADS, STORE_DEV>(c, src, dst, wr, wo, mid_word);
+        else launch_fused_kernel<S, true, FUSED_FP64_WIDE_THREADS, STORE_NT>(c, src, dst, wr, wo, mid_word);
     } else if (c->fused_threads == SMALL_THREADS) {             // below device-scope stores
-        if (st == STORE_CACHED) launch_fused_kernel<S, true, SMALL_THREADS, STORE_CACHED>(c, src, dst, wr, wo);
-        else launch_fused_kernel<S, true, SMALL_THREADS, STORE_NT>(c, src, dst, wr, wo);
+        if (st == STORE_CACHED) launch_fused_kernel<S, true, SMALL_THREADS, STORE_CACHED>(c, src, dst, wr, wo, mid_word);
+        else launch_fused_kernel<S, true, SMALL_THREADS, STORE_NT>(c, src, dst, wr, wo, mid_word);
     } else {
         FUSED(true, SITE_THREADS);
     }
@@ -386,12 +385,11 @@ lbm_status do_step_fused(lbm_ctx* c)
         s = ensure_wall_density<S>(c, c->cur);
         if (s) return s;
     }
-    launch_fused<S>(c, src, dst, c->wall_rho(c->wr_cur), c->wall_rho(1 - c->wr_cur), 2);
+    launch_fused<S>(c, src, dst, c->wall_rho(c->wr_cur), c->wall_rho(1 - c->wr_cur), 2, c->mid_word());
     s = check_launch(c, "step_fused");
     if (s) return s;
     c->cur = 1 - c->cur;
     c->have_prev = true;
-    c->prev_mid = false;
     if (walls) {
         c->wr_cur = 1 - c->wr_cur;
         c->wr_buf = c->cur;
@@ -458,7 +456,6 @@ lbm_status do_two_steps(lbm_ctx* c)
     if (s) return s;
     c->cur = 1 - c->cur;
     c->have_prev = true;
-    c->prev_mid = walls;
     if (walls) {
         c->wr_cur = 1 - c->wr_cur;
         c->wr_buf = c->cur;
@@ -640,7 +637,7 @@ lbm_status do_step_state(lbm_ctx* c, char* src, char* dst)
     const bool walls = c->p.ybc == LBM_Y_WALLS;
     const double* wr = walls ? (const double*)(src + c->pl.buf_bytes) : nullptr;
     double* wo = walls ? (double*)(dst + c->pl.buf_bytes) : nullptr;
-    launch_fused<S>(c, sb, db, wr, wo, CHAIN_BUFFERS);
+    launch_fused<S>(c, sb, db, wr, wo, CHAIN_BUFFERS, nullptr);
     return check_launch(c, "step_state");
 }
 
@@ -674,7 +671,7 @@ lbm_status do_advance_state(lbm_ctx* c, char* src, char* dst, int64_t n)
         } else {
             s = launch_pre_stream<S>(c, sb, false);
             if (s) return s;
-            launch_fused<S>(c, sb, db, wr, wo, src || dst ? CHAIN_BUFFERS : 2);
+            launch_fused<S>(c, sb, db, wr, wo, src || dst ? CHAIN_BUFFERS : 2, nullptr);
             s = check_launch(c, "advance_state");
         }
         if (s) return s;
@@ -808,7 +805,6 @@ lbm_status lbm_create(const lbm_params* p, void* dev_workspace, size_t bytes, vo
     c->stream = (hipStream_t)hip_stream;
     c->cur = 0;
     c->have_prev = false;
-    c->prev_mid = false;
     c->lam_cur = 0;
     c->have_lambda = false;
     c->lam_is_mu = false;

@@ -253,6 +253,16 @@ template <> struct VecA<double, 2> { typedef double T __attribute__((ext_vector_
 template <> struct VecA<float, 2> { typedef float T __attribute__((ext_vector_type(2))); };
 template <> struct VecA<float, 4> { typedef float T __attribute__((ext_vector_type(4))); };
 
+// Which table holds the wall densities of the state before the current one is
+// recorded on the device, not by the host: a replayed graph passes the host by.
+// A pass of two steps leaves them in a table of its own and sets the word
+// behind it (6 lx doubles on); single steps and propagates clear the word.  Every
+// kernel does so behind its stores, where nothing waits for it.
+__device__ __forceinline__ void set_mid_word(double* mid_word, double v)
+{
+    if (mid_word && blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) *mid_word = v;
+}
+
 // propagate: 256 threads, one 16-byte vector each, so a workgroup moves 4 KB
 // of one segment.  Loads and stores are both non-temporal (each byte is read
 // once and written once).  Workgroups are numbered linearly, chunk fastest,
@@ -278,7 +288,7 @@ constexpr unsigned PROP_GRID_X = 0xffffffffu / PROP_THREADS;
 
 template <typename S, int VEC, int UNROLL, bool WRAP, bool COLS, bool CACHED>
 __global__ __launch_bounds__(PROP_THREADS) void k_propagate(const S* __restrict__ src, S* __restrict__ dst, Geo g,
-                                                            unsigned nblk)
+                                                            unsigned nblk, double* __restrict__ mid_word)
 {
     using VU = typename VecT<S, VEC>::T;
     using VA = typename VecA<S, VEC>::T;
@@ -311,6 +321,7 @@ __global__ __launch_bounds__(PROP_THREADS) void k_propagate(const S* __restrict_
         if (CACHED) *reinterpret_cast<VA*>(dp + y) = (VA)v[u];
         else st_nt<VA>(reinterpret_cast<VA*>(dp), (unsigned)y * (unsigned)sizeof(S), (VA)v[u]);
     }
+    set_mid_word(mid_word, 0.0);
 }
 
 // x halos for LBM_X_HALO: copy whole padded columns into the 3 halo columns
@@ -373,9 +384,12 @@ __global__ __launch_bounds__(WALL_DENSITY_THREADS) void k_wall_density(const S* 
 }
 
 // Wall rule on the current buffer (split step): thread per (column, slot).
+// wall_mid: the table of the passes of two steps, or NULL where there are none.
 template <typename S>
-__global__ __launch_bounds__(256) void k_bc_apply(S* __restrict__ dst, Geo g, const double* __restrict__ wall_rho, WallTable wt)
+__global__ __launch_bounds__(256) void k_bc_apply(S* __restrict__ dst, Geo g, const double* __restrict__ wall_prev,
+                                                  const double* __restrict__ wall_mid, WallTable wt)
 {
+    const double* wall_rho = wall_mid && wall_mid[6 * g.lx] != 0.0 ? wall_mid : wall_prev;
     const int t = blockIdx.x * 256 + threadIdx.x;
     if (t >= NSLOT * g.lx) return;
     const int j = t % NSLOT, x = t / NSLOT;
@@ -547,7 +561,7 @@ constexpr unsigned COLLIDE_FP32_LDS_RESERVE = 64 * 1024;
 template <typename S, bool WRAP, bool WALLS, bool WIDE = true, int T = SITE_THREADS, StoreKind ST = STORE_DEV>
 __global__ __launch_bounds__(T) void k_step_fused(const S* __restrict__ src, S* __restrict__ dst, Geo g,
                                                   CollideArgs args, const double* __restrict__ wall_rho, WallTable wt,
-                                                  double* __restrict__ wall_rho_out)
+                                                  double* __restrict__ wall_rho_out, double* __restrict__ mid_word)
 {
     using Cc = typename Store<S>::C;
     const SiteBlock sb = site_block<sizeof(S) == 8, T>(g);
@@ -594,6 +608,7 @@ __global__ __launch_bounds__(T) void k_step_fused(const S* __restrict__ src, S* 
 #pragma unroll
     for (int l = 0; l < NPOP; ++l) st_stream<ST>(out + (size_t)l * g.ps, yb, (S)f[l]);
     if (WALLS) store_wall_density<S>(f, g, x, y, wall_rho_out);
+    if (WALLS) set_mid_word(mid_word, 0.0);
 }
 
 // ---------------------------------------------------------------------------

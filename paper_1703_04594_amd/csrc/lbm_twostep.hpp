@@ -200,6 +200,7 @@ __global__ __launch_bounds__((tile_threads<TX, TY>()), WIDE ? 4 : 6) void k_twos
             if (near) wall_rho_out[(y < 3 ? r : 3 + r) * g.lx + X] = stored_density<S>(f);
         }
     }
+    if (WALLS) set_mid_word(wall_mid + 6 * g.lx, 1.0);
 }
 
 // ---------------------------------------------------------------------------
@@ -511,6 +512,7 @@ __global__ __launch_bounds__(2 * MarchShape<S>::waves * 64) void k_twostep_march
             body(fb, fa, i);
             if (++i == ncol) break;
         }
+        if (WALLS) set_mid_word(wall_mid + 6 * g.lx, 1.0);
     } else {
         // ---- second step
         const int r = min(t - NW * 64, NY - 1);

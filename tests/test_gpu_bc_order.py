@@ -33,3 +33,47 @@ def test_bc_is_refused_after_an_advance(n, source, target):
         lat.bc()
     lat.propagate()
     lat.bc()
+
+
+# A replay advances the state without the host: eager steps and replays of both
+# kinds (single steps, passes of two) before the bc, an even number each, so that
+# the graph's buffers are those it was captured with.  "c4": capture of 4 steps,
+# "r": its replay, "4": eager steps.
+ORDERS = [["2", "c4", "r", "2", "r"], ["2", "c4", "r", "2"], ["2", "c2", "r", "4", "r"], ["2", "c2", "4", "r", "4"],
+          ["4", "c2"], ["2", "c4"], ["2", "c6", "4", "r", "r", "8"]]
+
+
+@pytest.mark.parametrize("order", ORDERS, ids="-".join)
+@pytest.mark.parametrize("lx,ly,precision", [(40, 33, "fp64"), (129, 257, "fp32"), (901, 1458, "fp32")])
+def test_bc_among_replays_equals_single_steps(lx, ly, precision, order):
+    say(f"bc among replays {lx}x{ly} {precision} {order}")
+    s = torch.cuda.Stream()
+    with torch.cuda.stream(s):
+        a, b = (lattice(lx, ly, precision=precision) for _ in range(2))
+    graph, n = None, 0
+    for op in order:
+        if op[0] == "c":
+            graph, n = torch.cuda.CUDAGraph(), int(op[1:])
+            s.synchronize()
+            with torch.cuda.graph(graph, stream=s):
+                a.step(n)
+            continue
+        with torch.cuda.stream(s):
+            if op == "r":
+                graph.replay()
+            else:
+                a.step(int(op))
+            for _ in range(n if op == "r" else int(op)):
+                b.step(1)
+    with torch.cuda.stream(s):
+        a.bc()
+        b.bc()
+        after_bc = [x.get_pops() for x in (a, b)]
+        a.step(1)
+        b.step(1)
+        after_step = [x.get_pops() for x in (a, b)]
+        a.bc()
+        b.bc()
+        last = [x.get_pops() for x in (a, b)]
+    s.synchronize()
+    assert torch.equal(*after_bc) and torch.equal(*after_step) and torch.equal(*last)
