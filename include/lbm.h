@@ -263,7 +263,8 @@ lbm_status lbm_adjoint_take_dtau(lbm_ctx* ctx, double* dev_dtau_acc);
 /* dP <- dL/dP for the initial state of lbm_init_rt(P, prof), from lambda_0. */
 lbm_status lbm_adjoint_init_rt(lbm_ctx* ctx, const double* P,
                                const lbm_rt_profile* prof, double* dP);
-/* Canonical FP64 [37][lx][ly] copies of lambda (device). */
+/* Canonical FP64 [37][lx][ly] copies of lambda (device).  A lambda that was
+ * neither seeded nor set reads as zeros. */
 lbm_status lbm_adjoint_get_lambda(lbm_ctx* ctx, double* dst);
 lbm_status lbm_adjoint_set_lambda(lbm_ctx* ctx, const double* src);
 

@@ -421,6 +421,12 @@ __global__ __launch_bounds__(SITE_THREADS) void k_adj_init_rt(const L* __restric
     dP[s] = acc;
 }
 
+// the canonical array of a lambda that was never seeded
+__global__ __launch_bounds__(256) void k_zero(double* __restrict__ p, size_t n)
+{
+    for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (size_t)gridDim.x * 256) p[i] = 0.0;
+}
+
 // lambda (load_lambda) -> canonical FP64 [37][lx][ly], one thread per site
 template <typename L, bool WALLS, bool GATHER>
 __global__ __launch_bounds__(SITE_THREADS) void k_lambda_to_canon(const L* __restrict__ buf, Geo lg, WallTable wt,
