@@ -558,17 +558,20 @@ void launch_canon(lbm_ctx* c, S* canon)
     const int nv = (g.ly + VEC - 1) / VEC;
     int lts = 0;
     while (lts < 8 && (1 << lts) < nv) ++lts;
-    const unsigned nch = (unsigned)((nv + CANON_THREADS - 1) / CANON_THREADS);
-    const size_t spb = (size_t)CANON_THREADS >> lts;
+    const int waves = (nv + 63) / 64;
+    const unsigned nch = (unsigned)((waves + CANON_THREADS / 64 - 1) / (CANON_THREADS / 64));
+    // chunks of a long segment in as few waves as its vectors fill
+    const int threads = nch == 1 ? CANON_THREADS : (waves + (int)nch - 1) / (int)nch * 64;
+    const size_t spb = nch == 1 ? (size_t)CANON_THREADS >> lts : 1;
     const size_t nblk = (((size_t)NPOP * g.lx + spb - 1) / spb) * nch;
     const unsigned gx = nblk < PROP_GRID_X ? (unsigned)nblk : PROP_GRID_X;
     const dim3 grid(gx, (unsigned)((nblk + gx - 1) / gx));
     // segments in the order of the array that is written
     if (!TO_CANON && c->p.layout == LBM_LAYOUT_COLUMNS)
-        hipLaunchKernelGGL((k_canon_copy<S, TO_CANON, true, NT>), grid, dim3(CANON_THREADS), 0, c->stream,
+        hipLaunchKernelGGL((k_canon_copy<S, TO_CANON, true, NT>), grid, dim3(threads), 0, c->stream,
                            (S*)c->buf(c->cur), canon, g, lts, nch, (unsigned)nblk);
     else
-        hipLaunchKernelGGL((k_canon_copy<S, TO_CANON, false, NT>), grid, dim3(CANON_THREADS), 0, c->stream,
+        hipLaunchKernelGGL((k_canon_copy<S, TO_CANON, false, NT>), grid, dim3(threads), 0, c->stream,
                            (S*)c->buf(c->cur), canon, g, lts, nch, (unsigned)nblk);
 }
 template <typename S>

@@ -700,13 +700,16 @@ __global__ __launch_bounds__(SITE_THREADS) void k_macros(const S* __restrict__ b
 // canonical [37][lx][ly] <-> padded: 16-byte vectors, one per thread.  A
 // segment (one population of one column) takes ts threads, a power of two, so
 // a block of 256 copies 256 / ts whole segments, or one of nch chunks of a
-// long one.  Canonical rows start wherever ly puts them: their vectors are
-// accessed unaligned (legal on CDNA for dword-aligned addresses), the padded
-// side's are aligned.  Segments run in the order of the array that is written:
-// the buffer's (BUFSEQ) or the canonical one (1024 x 2048 FP64: set 196 us
-// against 218, get 197 against 202).  NT: non-temporal, for arrays beyond the
-// caches.  Bound by HBM: 6.3 TB/s at 1024 x 2048 FP64 (with one element per
-// thread 4.6-5.1), 6.3 at 2048 x 4096 FP32 (2.8).
+// long one, in waves that are all but the last full (us per copy out and in,
+// FP64, with chunks of 256 vectors / of even waves: 513x513 32 and 32 / 26 and
+// 27, 640x640 41 and 41 / 35 and 35, 700x1111 89 and 84 / 81 and 77).  Canonical
+// rows start wherever ly puts them: their vectors are accessed unaligned (legal
+// on CDNA for dword-aligned addresses), the padded side's are aligned.  Segments
+// run in the order of the array that is written: the buffer's (BUFSEQ) or the
+// canonical one (1024 x 2048 FP64: set 196 us against 218, get 197 against 202).
+// NT: non-temporal, for arrays beyond the caches.  Bound by HBM: 6.3 TB/s at
+// 1024 x 2048 FP64 (with one element per thread 4.6-5.1), 6.3 at 2048 x 4096
+// FP32 (2.8).
 constexpr int CANON_THREADS = 256;
 template <typename S, bool TO_CANON, bool BUFSEQ, bool NT>
 __global__ __launch_bounds__(CANON_THREADS) void k_canon_copy(S* __restrict__ buf, S* __restrict__ canon, Geo g,
@@ -720,7 +723,7 @@ __global__ __launch_bounds__(CANON_THREADS) void k_canon_copy(S* __restrict__ bu
     const unsigned t = threadIdx.x;
     const long long seg = ((long long)(L / nch) << (8 - lts)) + (t >> lts);
     if (seg >= (long long)NPOP * g.lx) return;
-    const int y = (int)(((L % nch) * CANON_THREADS + (t & ((1u << lts) - 1))) * VEC);
+    const int y = (int)(((L % nch) * blockDim.x + (t & ((1u << lts) - 1))) * VEC);
     if (y >= g.ly) return;
     const int l = (int)(BUFSEQ ? seg % NPOP : seg / g.lx), x = (int)(BUFSEQ ? seg / NPOP : seg % g.lx);
     S* b = buf + (size_t)l * g.ps + g.origin + (long long)x * g.cs + y;

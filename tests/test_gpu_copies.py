@@ -79,3 +79,22 @@ def test_initial_states_and_read_outs(lx, ly, precision):
         assert float((a - b).abs().max()) <= tol
     tot = torch.stack([rho.sum(), j[0].sum(), j[1].sum(), en.sum()])
     assert bool(((lat.conservation() - tot).abs() <= tol * lx * ly).all())
+
+
+# segments of 4 to 9 waves of vectors: chunks of fewer waves than a block has,
+# the last wave full, with one vector, with one element
+@pytest.mark.parametrize("rows", [256, 257, 320, 321, 384, 449, 512, 513, 576])
+@pytest.mark.parametrize("tail", [0, 1])
+@pytest.mark.parametrize("precision", ["fp64", "fp32"])
+def test_copies_of_long_segments(rows, tail, precision):
+    lx, ly = 9, rows * (2 if precision == "fp64" else 4) - tail
+    say(f"long segments {lx}x{ly} {precision}")
+    dt = torch.float64 if precision == "fp64" else torch.float32
+    lat = Lattice(lx, ly, TAU, G, TB, TT, precision=precision, device=DEV)
+    n = 37 * lx * ly
+    f = torch.arange(n, device=DEV, dtype=torch.float64).to(dt).reshape(37, lx, ly)
+    lat.set_pops(f)
+    guard = torch.full((n + 64,), -7.0, dtype=dt, device=DEV)
+    lat._run("get_pops", lat.L.lbm_get_pops, guard[32:32 + n].data_ptr())
+    assert torch.equal(guard[32:32 + n], f.reshape(-1))
+    assert bool((guard[:32] == -7.0).all()) and bool((guard[32 + n:] == -7.0).all())
