@@ -503,9 +503,18 @@ lbm_status do_step(lbm_ctx* c, int64_t n)
 constexpr size_t COPY_NT_MIN_BYTES = 128u << 20;
 
 // Kernels that only read or only write a population buffer take non-temporal
-// accesses where the buffer alone exceeds the Infinity Cache (1000 x 1501 FP32,
-// 233 MB: init 35 us without and 45 with them, macros 37 and 55).
-constexpr size_t STREAM_NT_MIN_BYTES = 256u << 20;
+// accesses where the 64-byte pieces of its sites are well beyond the Infinity
+// Cache.  us without and with them, sites' pieces in MB (10^6 bytes): init FP64
+// 20000x33 (237) 55 / 69, 950x950 (270) 46 / 54, 17x60000 (302) 49 / 56, 1050x1000
+// (311) 57 / 56, 1100x1000 (326) 67 / 58, 1024x2048 (621) 170 / 127; FP32, whose
+// short rows leave most of a line unwritten, 100000x7 (237) 97 / 153, 60000x17
+// (284) 80 / 140, 200000x7 (474) 338 / 306; macros FP64 950x950 45 / 52, 1050x1000 62
+// / 58.
+constexpr size_t STREAM_NT_MIN_BYTES = 300u << 20;
+bool streamed(const Geo& g, size_t elem)
+{
+    return NPOP * (size_t)g.lx * align_up((size_t)g.ly * elem, 64) >= STREAM_NT_MIN_BYTES;
+}
 
 // the state was set, with its wall densities where there are walls
 void state_initialised(lbm_ctx* c)
@@ -517,7 +526,7 @@ template <typename S>
 lbm_status do_init(lbm_ctx* c, const double* rho, const double* ux, const double* uy, const double* T)
 {
     double* wr = c->p.ybc == LBM_Y_WALLS ? c->wall_rho(c->wr_cur) : nullptr;
-    if (c->pl.buf_bytes >= STREAM_NT_MIN_BYTES)
+    if (streamed(c->pl.geo, sizeof(S)))
         hipLaunchKernelGGL((k_init_fields<S, true>), site_grid(c->pl.geo), dim3(SITE_THREADS), 0, c->stream,
                            (S*)c->buf(c->cur), c->pl.geo, rho, ux, uy, T, wr);
     else
@@ -530,7 +539,7 @@ template <typename S>
 lbm_status do_init_rt(lbm_ctx* c, const double* P, RtProfile pr)
 {
     double* wr = c->p.ybc == LBM_Y_WALLS ? c->wall_rho(c->wr_cur) : nullptr;
-    if (c->pl.buf_bytes >= STREAM_NT_MIN_BYTES)
+    if (streamed(c->pl.geo, sizeof(S)))
         hipLaunchKernelGGL((k_init_rt<S, true>), site_grid(c->pl.geo), dim3(SITE_THREADS), 0, c->stream,
                            (S*)c->buf(c->cur), c->pl.geo, P, pr, wr);
     else
@@ -542,7 +551,7 @@ lbm_status do_init_rt(lbm_ctx* c, const double* P, RtProfile pr)
 template <typename S>
 lbm_status do_macros(lbm_ctx* c, double* rho, double* ux, double* uy, double* T)
 {
-    if (c->pl.buf_bytes >= STREAM_NT_MIN_BYTES)
+    if (streamed(c->pl.geo, sizeof(S)))
         hipLaunchKernelGGL((k_macros<S, true>), site_grid(c->pl.geo), dim3(SITE_THREADS), 0, c->stream,
                            (const S*)c->buf(c->cur), c->pl.geo, rho, ux, uy, T);
     else
@@ -692,7 +701,7 @@ lbm_status do_advance_state(lbm_ctx* c, char* src, char* dst, int64_t n)
 template <typename S>
 void launch_conservation_partial(const Geo& g, const S* buf, double* part, hipStream_t st)
 {
-    if (g.ly % 64 == 0 && (size_t)g.total * sizeof(S) >= STREAM_NT_MIN_BYTES)
+    if (g.ly % 64 == 0 && streamed(g, sizeof(S)))
         hipLaunchKernelGGL((k_conservation_partial<S, true>), dim3(RED_BLOCKS), dim3(256), 0, st, buf, g, part);
     else
         hipLaunchKernelGGL((k_conservation_partial<S, false>), dim3(RED_BLOCKS), dim3(256), 0, st, buf, g, part);
