@@ -993,6 +993,17 @@ lbm_status lbm_advance_state(lbm_ctx* c, void* src_state, void* dst_state, int64
     return DISPATCH(c, do_advance_state, (char*)src_state, (char*)dst_state, n);
 }
 
+lbm_two_step lbm_two_step_form(const lbm_ctx* c)
+{
+    switch (c ? c->two.kind : TWO_STEP_NONE) {
+    case TWO_STEP_TILE_8X8: return LBM_TWO_STEP_TILE_8X8;
+    case TWO_STEP_TILE_8X16: return LBM_TWO_STEP_TILE_8X16;
+    case TWO_STEP_TILE_16X16: return LBM_TWO_STEP_TILE_16X16;
+    case TWO_STEP_MARCH: return LBM_TWO_STEP_MARCH;
+    default: return LBM_TWO_STEP_NONE;
+    }
+}
+
 lbm_status lbm_conservation(lbm_ctx* c, double* dev_out4)
 {
     if (!c) return LBM_ERR_INVALID;

@@ -1,7 +1,7 @@
-/* lbm_rollout.h -- entry points that the package's checkpointed rollout calls
- * besides the C ABI of lbm.h: whole pieces of a schedule in fewer passes over
- * memory than its single calls take.  The binding's own; a user's program has
- * everything it needs in lbm.h. */
+/* lbm_rollout.h -- entry points that the package calls besides the C ABI of
+ * lbm.h: whole pieces of a rollout's schedule in fewer passes over memory than
+ * its single calls take, and which kernels a context's steps take.  The
+ * binding's own; a user's program has everything it needs in lbm.h. */
 #ifndef LBM_ROLLOUT_H
 #define LBM_ROLLOUT_H
 
@@ -20,6 +20,16 @@ extern "C" {
  * one pass was enough).  lbm_bc needs a propagate first, as after
  * lbm_set_state. */
 lbm_status lbm_advance_state(lbm_ctx* ctx, void* src_state, void* dst_state, int64_t n);
+
+/* How lbm_step takes two steps in one pass over memory in this context. */
+typedef enum {
+    LBM_TWO_STEP_NONE = 0,      /* it does not: single steps */
+    LBM_TWO_STEP_TILE_8X8 = 1,  /* tiles of that many columns and rows */
+    LBM_TWO_STEP_TILE_8X16 = 2,
+    LBM_TWO_STEP_TILE_16X16 = 3,
+    LBM_TWO_STEP_MARCH = 4      /* a march along x */
+} lbm_two_step;
+lbm_two_step lbm_two_step_form(const lbm_ctx* ctx);
 
 #ifdef __cplusplus
 }

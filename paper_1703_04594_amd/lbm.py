@@ -30,6 +30,7 @@ _PREC = {"fp64": FP64, "fp32": FP32_SHIFTED, "fp32_shifted": FP32_SHIFTED, "fp32
 _YBC = {"walls": Y_WALLS, "periodic": Y_PERIODIC}
 _XMODE = {"wrap": X_WRAP, "halo": X_HALO}
 _STEP = {"split": STEP_SPLIT, "fused": STEP_FUSED}
+_TWO_STEP = ("none", "tile 8x8", "tile 8x16", "tile 16x16", "march")
 _LAYOUT = {"planes": LAYOUT_PLANES, "columns": LAYOUT_COLUMNS}
 
 
@@ -100,6 +101,8 @@ def lib() -> ctypes.CDLL:
     L.lbm_adjoint_step.argtypes = [vp, vp, vp]
     L.lbm_step_state.argtypes = [vp, vp, vp]
     L.lbm_advance_state.argtypes = [vp, vp, vp, i64]
+    L.lbm_two_step_form.argtypes = [vp]
+    L.lbm_two_step_form.restype = ctypes.c_int
     L.lbm_adjoint_init_rt.argtypes = [vp, vp, ctypes.POINTER(RtProfileC), vp]
     L.lbm_last_error.argtypes = [vp]
     L.lbm_last_error.restype = ctypes.c_char_p
@@ -314,6 +317,11 @@ class Lattice:
         ps, pd = (ctypes.c_void_p(_ptr(t, torch.uint8, (self.state_bytes,), self.device)) if t is not None else None
                   for t in (src, dst))
         self._run("advance_state", self.L.lbm_advance_state, ps, pd, int(n))
+
+    def two_step_form(self) -> str:
+        """How step(n) takes two steps in one pass over memory here: "none",
+        "tile 8x8", "tile 8x16", "tile 16x16" or "march"."""
+        return _TWO_STEP[self.L.lbm_two_step_form(self.h)]
 
     def conservation(self) -> torch.Tensor:
         out = torch.empty(4, dtype=torch.float64, device=self.device)
