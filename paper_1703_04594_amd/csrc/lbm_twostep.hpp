@@ -25,6 +25,8 @@
 // included, so n steps are bitwise those of n single steps.
 #pragma once
 
+#include <type_traits>
+
 #include "lbm_kernels.hpp"
 
 namespace lbm {
@@ -88,15 +90,22 @@ constexpr int tile_threads() { return ((TX + 6) * (TY + 6) + 63) / 64 * 64; }
 // scalar loads ahead of the gather, and spills it (us per step, before and
 // after: FP64 128x128 4.8 -> 4.4, 256x128 5.9 -> 5.3, 256x256 7.3 -> 6.6, FP32 384x384
 // 10.9 -> 10.1; the single step and the reverse step, which had fewer rounds, gain
-// nothing).  TileArgs mirrors the segment: the kernel's parameters in order.
-template <typename S>
-struct TileArgs { const S* src; S* dst; Geo g; CollideArgs args; const double* wall_rho; WallTable wt; };
+// nothing).  Where it lies in the segment follows from the kernel's signature:
+// arguments in order, each aligned as its type.
+template <typename T, typename... P>
+constexpr size_t kernarg_offset(void (*)(P...))
+{
+    size_t off = 0, at = 0;
+    ((off = (off + alignof(P) - 1) / alignof(P) * alignof(P), at = std::is_same<T, P>::value ? off : at, off += sizeof(P)),
+     ...);
+    return at;
+}
 typedef const __attribute__((address_space(4))) char* kernarg_t;
 typedef const __attribute__((address_space(4))) WallTable wall_table_arg_t;
-template <typename S>
-__device__ __forceinline__ wall_table_arg_t& tile_wall_table()
+template <size_t OFFSET>
+__device__ __forceinline__ wall_table_arg_t& wall_table_arg()
 {
-    kernarg_t p = (kernarg_t)__builtin_amdgcn_kernarg_segment_ptr() + offsetof(TileArgs<S>, wt);
+    kernarg_t p = (kernarg_t)__builtin_amdgcn_kernarg_segment_ptr() + OFFSET;
     asm volatile("" : "+s"(p));   // not loaded ahead of this point
     return *(wall_table_arg_t*)p;
 }
@@ -107,6 +116,8 @@ __global__ __launch_bounds__((tile_threads<TX, TY>()), WIDE ? 4 : 6) void k_twos
     WallTable wt, double* __restrict__ wall_mid, double* __restrict__ wall_rho_out)
 {
     using Cc = typename Store<S>::C;
+    constexpr size_t WT_AT = kernarg_offset<WallTable>((decltype(&k_twostep_tile<S, WALLS, WIDE, TX, TY>))nullptr);
+    static_assert(WT_AT != 0, "wt is an argument, and not the first");
     __shared__ S post[NPOP][TX * TY];                // the first step, by the second step's sites
     __shared__ double wr[WALLS ? 6 : 1][TX + 6];     // its wall densities
     const int nty = (g.ly + TY - 1) / TY, ntx = (g.lx + TX - 1) / TX;
@@ -150,7 +161,7 @@ __global__ __launch_bounds__((tile_threads<TX, TY>()), WIDE ? 4 : 6) void k_twos
                 soff += stride;
             }
             if (near) {
-                auto& w = tile_wall_table<S>();
+                auto& w = wall_table_arg<WT_AT>();
                 if (y < 3) put_wall_slots<S, 0>(f, r, w, d);
                 else put_wall_slots<S, 1>(f, r, w, d);
             }
@@ -184,7 +195,7 @@ __global__ __launch_bounds__((tile_threads<TX, TY>()), WIDE ? 4 : 6) void k_twos
                 double d[NWS];
 #pragma unroll
                 for (int j = 0; j < NWS; ++j) d[j] = wr[WALLS ? w0 + max(WH.en[j] - 1 - r, 0) : 0][ox + 3 - WH.ex[j]];
-                auto& w = tile_wall_table<S>();
+                auto& w = wall_table_arg<WT_AT>();
                 if (y < 3) put_wall_slots<S, 0>(f, r, w, d);
                 else put_wall_slots<S, 1>(f, r, w, d);
             }
