@@ -845,8 +845,9 @@ lbm_status lbm_create(const lbm_params* p, void* dev_workspace, size_t bytes, vo
         c->dev_stores = dev_stores_for(site_grid(pl.geo).x, ncu);
         if (fl.lds == 0 && !c->dev_stores && few_rows_fill(p->ly)) c->fused_threads = SMALL_THREADS;
         if (p->step_kind == LBM_STEP_FUSED)
-            c->two = p->precision == LBM_FP64 ? choose_two_step<double>(pl.geo, ncu, max_lds, p->ybc == LBM_Y_WALLS)
-                                              : choose_two_step<float>(pl.geo, ncu, max_lds, p->ybc == LBM_Y_WALLS);
+            c->two = p->precision == LBM_FP64
+                         ? choose_two_step<double>(pl.geo, ncu, max_lds, p->ybc == LBM_Y_WALLS, false)
+                         : choose_two_step<float>(pl.geo, ncu, max_lds, p->ybc == LBM_Y_WALLS, c->f32_sums());
         if ((size_t)site_grid(pl.geo).x >= (size_t)FUSED_FP64_CAP_MIN_BLOCKS_PER_CU * (size_t)ncu) {
             const unsigned coll = p->precision == LBM_FP64 ? COLLIDE_FP64_LDS_RESERVE : COLLIDE_FP32_LDS_RESERVE;
             if ((size_t)max_lds >= coll && (p->precision != LBM_FP64 || p->layout == LBM_LAYOUT_COLUMNS))

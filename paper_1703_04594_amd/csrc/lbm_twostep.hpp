@@ -594,11 +594,22 @@ struct TwoStep { TwoStepKind kind; MarchLaunch march; };
 // (us per step, 8x8 / 8x16 / 16x16: FP64 128x128 4.7 / - / 6.2, 256x128 6.3 /
 // 5.9 / 6.6, 256x256 8.5 / 8.0 / 7.3 before the wall table was read late; FP32 4.8 / - / 5.5, 6.0 / 5.4 / 5.6, 8.0 / 7.1
 // / 6.0).
+// FP32 with FP64 sums, whose collisions bound it, takes 16 x 16 tiles only where
+// their rings' columns, 6 to a tile, are less than half of the lattice's (0.6 of
+// them up to four tiles per CU, any share up to the two that run at once).  us
+// per four steps, single / in pairs: 7x100000 158 / 193, 17x20000 73 / 99, 17x6000
+// 30 / 40, 33x10000 70 / 80, 24x40000 208 / 227; 33x5000 48 / 47, 12x12000 46 / 37,
+// 7x6000 24 / 23; 37x30000 234 / 169.
+inline bool few_columns(int lx, long long tiles, int ncu)
+{
+    const int ring = (lx + 15) / 16 * 6;
+    return ring * 2 >= lx && tiles > (ring * 10 >= lx * 6 ? 2 : 4) * ncu;
+}
 constexpr int MARCH_MIN_USE_PCT = 55;
 constexpr int TILE_FP32_MAX_SITES_PER_CU = 16 * 256;
 constexpr long long TILE_CACHE_BYTES = 256LL << 20;
 template <typename S>
-inline TwoStep choose_two_step(const Geo& g, int ncu, int max_lds, bool walls)
+inline TwoStep choose_two_step(const Geo& g, int ncu, int max_lds, bool walls, bool f32_sums)
 {
     TwoStep t{TWO_STEP_NONE, MarchLaunch{}};
     if (ncu <= 0) return t;
@@ -618,7 +629,7 @@ inline TwoStep choose_two_step(const Geo& g, int ncu, int max_lds, bool walls)
     auto tiles = [&](int tx, int ty) { return (long long)((g.lx + tx - 1) / tx) * ((g.ly + ty - 1) / ty); };
     if (tiles(8, 8) <= ncu) t.kind = TWO_STEP_TILE_8X8;
     else if (tiles(8, 16) <= ncu) t.kind = TWO_STEP_TILE_8X16;
-    else t.kind = TWO_STEP_TILE_16X16;
+    else if (sizeof(S) == 8 || f32_sums || !few_columns(g.lx, tiles(16, 16), ncu)) t.kind = TWO_STEP_TILE_16X16;
     return t;
 }
 

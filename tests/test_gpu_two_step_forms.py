@@ -68,3 +68,14 @@ def test_forms_equal_single_steps(lx, ly, precision, form, ybc):
     a.bc()
     b.bc()
     assert torch.equal(a.get_pops(), b.get_pops())
+
+
+# few columns: the tiles' rings are most of the work of a long lattice (FP32 with
+# FP64 sums alone), on both sides of the shares and of the numbers of tiles
+@pytest.mark.parametrize("lx,ly,form", [
+    (17, 4096, "tile 16x16"), (17, 4097, "none"), (20, 6000, "none"), (21, 6000, "tile 16x16"), (24, 8192, "tile 16x16"),
+    (24, 8193, "none"), (36, 5456, "tile 16x16"), (36, 5457, "none"), (37, 5457, "tile 16x16"), (7, 100000, "none")])
+def test_forms_of_few_columns(lx, ly, form):
+    assert lattice(lx, ly, precision="fp32").two_step_form() == form
+    assert lattice(lx, ly, precision="fp32_f32sums").two_step_form() == "tile 16x16"
+    assert lattice(lx, ly, precision="fp64").two_step_form() == "tile 16x16"
