@@ -601,7 +601,11 @@ lbm_status do_canon(lbm_ctx* c, void* canon, bool to_canon)
 lbm_status copy_state(lbm_ctx* c, const void* buf, void* to_buf, const void* wall, void* to_wall, size_t nw, const char* what)
 {
     const size_t na = c->pl.buf_bytes;
-    if (((uintptr_t)buf | (uintptr_t)to_buf) % 16) {   // a snapshot at an odd address (buf_bytes is a multiple of 256)
+    // the runtime's copy for a snapshot at an odd address (buf_bytes is a multiple of
+    // 256), and where it is one copy within the caches (us, it and the kernel: FP64
+    // without walls 64x64 3.8 and 4.2, 513x513 24.1 and 24.6, 700x700 63.5 and 48.6;
+    // with walls, two copies, 64x64 6.2 and 4.1)
+    if (((uintptr_t)buf | (uintptr_t)to_buf) % 16 || (!nw && na < COPY_NT_MIN_BYTES)) {
         if (hipMemcpyAsync(to_buf, buf, na, hipMemcpyDeviceToDevice, c->stream) != hipSuccess ||
             (nw && hipMemcpyAsync(to_wall, wall, nw, hipMemcpyDeviceToDevice, c->stream) != hipSuccess))
             return check_launch(c, what);

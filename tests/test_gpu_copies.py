@@ -98,3 +98,20 @@ def test_copies_of_long_segments(rows, tail, precision):
     lat._run("get_pops", lat.L.lbm_get_pops, guard[32:32 + n].data_ptr())
     assert torch.equal(guard[32:32 + n], f.reshape(-1))
     assert bool((guard[:32] == -7.0).all()) and bool((guard[32 + n:] == -7.0).all())
+
+
+# without walls a snapshot is the buffer alone: the runtime's copy below the
+# streaming bound, the kernel beyond it, and either at an odd address
+@pytest.mark.parametrize("lx,ly", [(7, 7), (40, 33), (700, 700)])
+@pytest.mark.parametrize("off", [256, 3])
+def test_snapshots_without_walls(lx, ly, off):
+    say(f"snapshots without walls {lx}x{ly} +{off}")
+    a, b = (Lattice(lx, ly, TAU, G, TB, TT, precision="fp64", ybc="periodic", device=DEV) for _ in range(2))
+    f = torch.arange(37 * lx * ly, device=DEV, dtype=torch.float64).reshape(37, lx, ly)
+    a.set_pops(f)
+    raw = torch.full((a.state_bytes + 1024,), 0x5A, dtype=torch.uint8, device=DEV)
+    st = raw[off:off + a.state_bytes]
+    a.get_state(st)
+    assert bool((raw[:off] == 0x5A).all()) and bool((raw[off + a.state_bytes:] == 0x5A).all())
+    b.set_state(st)
+    assert torch.equal(b.get_pops(), f)
