@@ -129,6 +129,8 @@ struct lbm_ctx {
     // the table of the states in between, and the word behind it; NULL where no
     // pass takes two steps or there are no walls
     double* wall_mid() { return two.kind != TWO_STEP_NONE && p.ybc == LBM_Y_WALLS ? wall_rho(WALL_MID) : nullptr; }
+    bool mid_may_be_set;  // the word may be 1: a pass of two steps has run since it was last cleared ...
+    bool two_captured;    // ... or may run at any time
     double* mid_word() { return wall_mid() ? wall_mid() + 6 * (size_t)p.lx : nullptr; }
     double* partials() { return reinterpret_cast<double*>(ws + pl.off_part); }
     double* scratch2() { return partials() + (size_t)RED_BLOCKS * 4; }
@@ -190,16 +192,16 @@ lbm_status launch_propagate_kind(lbm_ctx* c, const S* src, S* dst)
     const unsigned nb = (unsigned)nblk;
     if (wrap && cols)
         hipLaunchKernelGGL((k_propagate<S, VEC, UNROLL, true, true, CACHED>), grid, dim3(PROP_THREADS), 0, c->stream, src, dst, g,
-                           nb, c->mid_word());
+                           nb);
     else if (wrap)
         hipLaunchKernelGGL((k_propagate<S, VEC, UNROLL, true, false, CACHED>), grid, dim3(PROP_THREADS), 0, c->stream, src, dst, g,
-                           nb, c->mid_word());
+                           nb);
     else if (cols)
         hipLaunchKernelGGL((k_propagate<S, VEC, UNROLL, false, true, CACHED>), grid, dim3(PROP_THREADS), 0, c->stream, src, dst, g,
-                           nb, c->mid_word());
+                           nb);
     else
         hipLaunchKernelGGL((k_propagate<S, VEC, UNROLL, false, false, CACHED>), grid, dim3(PROP_THREADS), 0, c->stream, src, dst, g,
-                           nb, c->mid_word());
+                           nb);
     return check_launch(c, "propagate");
 }
 // the split step's kernels with cached loads and stores
@@ -256,6 +258,13 @@ lbm_status ensure_wall_density(lbm_ctx* c, int b)
     return LBM_OK;
 }
 
+bool capturing(lbm_ctx* c)
+{
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(c->stream, &st) != hipSuccess) (void)hipGetLastError();
+    return st != hipStreamCaptureStatusNone;
+}
+
 template <typename S>
 lbm_status do_propagate(lbm_ctx* c)
 {
@@ -263,6 +272,15 @@ lbm_status do_propagate(lbm_ctx* c)
     S* dst = (S*)c->buf(1 - c->cur);
     lbm_status s = launch_pre_stream<S>(c, src, true);
     if (s) return s;
+    if (c->mid_word()) {
+        const bool cap = capturing(c);   // passes of two steps may run before a replay
+        if (cap || c->mid_may_be_set) {
+            hipLaunchKernelGGL(k_zero, dim3(1), dim3(64), 0, c->stream, c->mid_word(), (size_t)1);
+            s = check_launch(c, "propagate");
+            if (s) return s;
+        }
+        if (!cap) c->mid_may_be_set = c->two_captured;
+    }
     s = launch_propagate<S>(c, src, dst);
     if (s) return s;
     if (c->wr_buf == 1 - c->cur) c->wr_buf = -1;   // destination overwritten
@@ -428,6 +446,7 @@ lbm_status launch_two_steps(lbm_ctx* c, const S* src, S* dst, const double* wr, 
 {
     const bool walls = c->p.ybc == LBM_Y_WALLS;
     double* mid = c->wall_rho(lbm_ctx::WALL_MID);
+    c->mid_may_be_set = true;
     if constexpr (std::is_same<S, float>::value) {
         if (c->f32_sums()) {
             if (walls) launch_two_step<S, true, false>(c, src, dst, wr, mid, wo);
@@ -469,7 +488,8 @@ lbm_status do_step(lbm_ctx* c, int64_t n)
     // Passes of two steps go in pairs, so that every four steps end on the
     // buffers they began with, as four single steps do (a graph of an even
     // number of steps can then be replayed).
-    if (c->p.step_kind == LBM_STEP_FUSED && c->two.kind != TWO_STEP_NONE) {
+    if (c->p.step_kind == LBM_STEP_FUSED && c->two.kind != TWO_STEP_NONE && n >= 4) {
+        c->two_captured = c->two_captured || capturing(c);
         for (; n >= 4; n -= 4) {
             lbm_status s = do_two_steps<S>(c);
             if (!s) s = do_two_steps<S>(c);
@@ -839,6 +859,8 @@ lbm_status lbm_create(const lbm_params* p, void* dev_workspace, size_t bytes, vo
     c->collide_lds = 0;
     c->dev_stores = false;
     c->two = TwoStep{TWO_STEP_NONE, MarchLaunch{}};
+    c->mid_may_be_set = false;
+    c->two_captured = false;
     int dev = 0, ncu = 0, max_lds = 0;
     if (hipGetDevice(&dev) == hipSuccess &&
         hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess &&

@@ -77,3 +77,45 @@ def test_bc_among_replays_equals_single_steps(lx, ly, precision, order):
         last = [x.get_pops() for x in (a, b)]
     s.synchronize()
     assert torch.equal(*after_bc) and torch.equal(*after_step) and torch.equal(*last)
+
+
+# propagate, bc and collide one by one after passes of two steps and replays of
+# them, and captured themselves: "p" the three kernels, "cp" a capture of them twice
+PIECES = [["4", "p", "p", "4", "p"], ["2", "c4", "p", "p", "r", "p"], ["2", "c4", "r", "p"], ["4", "cp", "p"],
+          ["2", "cp", "4", "r", "p", "p", "r"], ["2", "cp", "r", "4", "p"]]
+
+
+@pytest.mark.parametrize("order", PIECES, ids="-".join)
+@pytest.mark.parametrize("lx,ly,precision", [(40, 33, "fp64"), (129, 257, "fp32"), (901, 1458, "fp32")])
+def test_kernels_one_by_one_equal_steps(lx, ly, precision, order):
+    say(f"kernels one by one {lx}x{ly} {precision} {order}")
+    s = torch.cuda.Stream()
+    with torch.cuda.stream(s):
+        a, b = (lattice(lx, ly, precision=precision) for _ in range(2))
+
+    def pieces(times):
+        for _ in range(times):
+            a.propagate()
+            a.bc()
+            a.collide()
+
+    graph, n = None, 0
+    for op in order:
+        if op[0] == "c":
+            graph, n = torch.cuda.CUDAGraph(), 2 if op == "cp" else int(op[1:])
+            s.synchronize()
+            with torch.cuda.graph(graph, stream=s):
+                pieces(2) if op == "cp" else a.step(n)
+            continue
+        with torch.cuda.stream(s):
+            if op == "r":
+                graph.replay()
+            elif op == "p":
+                pieces(1)
+            else:
+                a.step(int(op))
+            for _ in range(n if op == "r" else 1 if op == "p" else int(op)):
+                b.step(1)
+            got, want = a.get_pops(), b.get_pops()
+        s.synchronize()
+        assert torch.equal(got, want), op
