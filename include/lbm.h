@@ -161,9 +161,11 @@ lbm_status lbm_bc(lbm_ctx* ctx);
  * moments (eq. (2)), gravity shift, equilibrium, f <- f + (f^eq - f)/tau. */
 lbm_status lbm_collide(lbm_ctx* ctx);
 /* n >= 0 times (propagate, bc, collide), split or fused per step_kind.
- * Fused steps run two to a pass over memory where n >= 4 allows (in groups of
- * four steps); the results are bitwise those of n single steps, for lbm_bc
- * after it too.
+ * Fused steps run two to a pass over memory, in groups of four steps: n = 4 k + r
+ * is 2 k passes and r single steps.  The results are bitwise those of n single
+ * steps, for lbm_bc after it too.  Lattices without such passes: FP64 ones in the
+ * planes layout from 2 GB per population buffer on (2048 x 4096: 2.2 times the
+ * time of the columns layout), and FP32 ones where they would not pay.
  * It only launches kernels on the context's stream, so it can be captured
  * into a HIP graph there (after at least one eager step).  A replay repeats
  * the captured launches with the buffers they were captured with: capture an
@@ -192,9 +194,9 @@ lbm_status lbm_set_state(lbm_ctx* ctx, const void* src);
  * receives the new state's wall densities too, so it can serve as the next
  * source or as an lbm_adjoint_step snapshot).  The sites and wall densities
  * of src_state are only read; its padding (x halo columns) is refreshed in
- * place for LBM_X_HALO.  The context's own population buffers are not touched.  Lets a checkpointed replay run from
- * snapshot to snapshot instead of stepping the context and copying its state
- * out. */
+ * place for LBM_X_HALO.  The context's own population buffers are not touched.
+ * Lets a checkpointed replay run from snapshot to snapshot instead of stepping
+ * the context and copying its state out. */
 lbm_status lbm_step_state(lbm_ctx* ctx, void* src_state, void* dst_state);
 /* Lattice totals of the collision invariants, accumulated in FP64 with a
  * fixed reduction order (bitwise reproducible): out4 = {sum rho, sum j_x,

@@ -69,29 +69,29 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t buf_of(S* base)
 // Tiles.  One thread per site of the first step (the tile and three rows and
 // columns around it); the tile's own sites, as many threads, run the second.
 // Without walls the gather wraps the row as it does the column, so a pass needs
-// no ghost rows (512 x 512: 2.6-3.6 us per pass for the launch that filled them).
+// no ghost rows.
 // What bounds a pass: on the smallest lattices the chain of one load, two
-// collisions and an LDS exchange (256 x 128 FP64: 10.5 us per two steps against
-// 13 us in single steps, without walls 9.2); above, the first step's work on the
-// rings (512 x 512: 33 us against 47 us FP64, 27.6 against 28.5 us FP32).
-// The buffer accesses keep one SGPR offset running over the populations: with
-// 64-bit column addresses 512 x 512 FP64 took 40.3 us, FP32 31.1.  The wall
-// densities are read ahead of the populations (behind them 128 x 128 FP64
-// +0.4 us).  Stores are plain: the next pass reads them from the caches (with
-// non-temporal ones 512 x 512 FP64 took 10 us more).  With FP32 sums 80
-// registers are enough for six waves per SIMD (384 x 384 without walls: 18.9 us
-// against 21.1 with 128); the FP64 sums would spill (27 us against 22).
+// collisions and an LDS exchange (256 x 128 FP64: 10.3 us per two steps against
+// 12.1 in single steps); above, the first step's work on the rings (512 x 512 FP64:
+// 33 us against 47, FP32 27.4 against 28.2).
+// The buffer accesses keep one SGPR offset running over the populations (with
+// 64-bit column addresses 512 x 512 FP64 took 40 us).  The wall densities are read
+// ahead of the populations.  Stores are plain: the next pass reads them from the
+// caches.  With FP32 sums 80 registers are enough for six waves per SIMD; with
+// walls they spill 12 bytes a lane (us per step, five waves without spills / six:
+// with walls 128x128 4.43 / 4.61, 384x384 9.55 / 8.79, 640x640 17.1 / 16.8; without
+// walls 384x384 9.49 / 8.17).  The FP64 sums would spill 95 registers.
 // ---------------------------------------------------------------------------
 template <int TX, int TY>
 constexpr int tile_threads() { return ((TX + 6) * (TY + 6) + 63) / 64 * 64; }
 
 // The tile kernel's wall table, read from its argument segment where it is
 // used: as a plain argument the compiler loads it on entry, in several rounds of
-// scalar loads ahead of the gather, and spills it (us per step, before and
-// after: FP64 128x128 4.8 -> 4.4, 256x128 5.9 -> 5.3, 256x256 7.3 -> 6.6, FP32 384x384
-// 10.9 -> 10.1; the single step and the reverse step, which had fewer rounds, gain
-// nothing).  Where it lies in the segment follows from the kernel's signature:
-// arguments in order, each aligned as its type.
+// scalar loads ahead of the gather, and spills it (us per step, as an argument and
+// so: FP64 128x128 4.8 and 4.4, 256x256 7.3 and 6.6, FP32 384x384 10.9 and 10.1; the
+// single step and the reverse step, which have fewer rounds, gain nothing).  Where
+// it lies in the segment follows from the kernel's signature: arguments in order,
+// each aligned as its type.
 template <typename T, typename... P>
 constexpr size_t kernarg_offset(void (*)(P...))
 {
@@ -232,12 +232,9 @@ __global__ __launch_bounds__((tile_threads<TX, TY>()), WIDE ? 4 : 6) void k_twos
 // MARCH_LOADS_EARLY of them go out before barrier 1: 24-28 of 37 in FP64 (all
 // after it 1,020 us per two steps at 2048 x 4096, half 936, 28 of them 891, all
 // before it 982), few in FP32, whose two waves per SIMD cover them.
-// What bounds it now: in FP64 HBM (2048 x 4096: 0.44 ms per step against 0.83
-// in single steps; 5.6 TB/s, reads and writes within 1-4% of one each per
-// population and pass); in FP32 the vector units (0.27 ms against 0.44).
-// Other forms measured slower (2048 x 4096 FP64, us per two steps): both steps
-// on the same waves with a barrier between them 1,591; loads in one burst
-// 1,150; strips of 96 rows 912, of 64 rows and two blocks per CU 1,144.
+// What bounds it: in FP64 HBM (2048 x 4096: 0.435 ms per step against 0.81 in
+// single steps; 5.6 TB/s, reads and writes within 1-4% of one each per population
+// and pass); in FP32 the vector units (0.26 ms against 0.43).
 // ---------------------------------------------------------------------------
 // LDS barrier that leaves global loads and stores in flight
 __device__ __forceinline__ void lds_barrier()
@@ -581,19 +578,19 @@ struct TwoStep { TwoStepKind kind; MarchLaunch march; };
 // Tiles where both buffers stay in the 256 MB Infinity Cache, which covers what
 // they read twice; beyond it the march, where its blocks' lanes and columns are
 // mostly used: sites over (columns the slowest block steps x rows x CUs) of at
-// least 0.55.  Measured, us per step, march / tiles (padded buffers in MB, with
-// walls unless noted): FP64 400x1000 (242) 29.7 / 28.2, 640x640 (239) 32.9 /
-// 28.6, 680x680 (266) 37.6 / 36.5, without walls 33.7 / 35.6, 720x720 (296) 39.5 /
-// 42.3, 1024x1024 (592) 67 / 79; FP32 850x850 (213) 31.9 / 31.7 and with FP32
-// sums 29.5 / 25.4, 900x900 (237) 38.6 / 34.9, 930x930 (254) 41.7 / 42.2,
-// 1024x1024 (306) 50 / 58.  Beyond the cache and below that share tiles still
-// gain on single steps in FP64 (2048x4096: 1287 us per two steps against 1660);
-// in FP32, whose collisions are the larger part of a step, up to 16 x 256 sites
-// per CU (1024x1024: 115 against 123; 2048x4096: 957 against 862).
-// The smallest tiles are taken while they leave no CU with more than one
-// (us per step, 8x8 / 8x16 / 16x16: FP64 128x128 4.7 / - / 6.2, 256x128 6.3 /
-// 5.9 / 6.6, 256x256 8.5 / 8.0 / 7.3 before the wall table was read late; FP32 4.8 / - / 5.5, 6.0 / 5.4 / 5.6, 8.0 / 7.1
-// / 6.0).
+// least 0.55.  us per step, tiles / march with walls, and without (padded buffers
+// in MB): FP64 640x640 (239) 26 / 32 and 27 / 30, 680x680 (266) 36 / 38 and 37 / 34,
+// 720x720 (296) 41 / 40 and 41 / 38, 1024x1024 (592) 78 / 67 and 77 / 65; FP32 900x900
+// (237) 33 / 38 and 34 / 34, 930x930 (254) 41 / 42 and 40 / 37, 1024x1024 (306) 56 / 49
+// and 51 / 43; with FP32 sums 900x900 31 / 37 and 29 / 33, 1024x1024 52 / 47 and 49 / 42.
+// Beyond the cache and below that share tiles still gain on single steps in FP64
+// (20000x33: 80 us per step against 300, the march 129; 1024x1024 78 against 111);
+// in FP32, whose collisions are the larger part of a step, up to 16 x 256 sites per
+// CU (1024x1024 56 against 56, with FP32 sums 52 against 56; 2048x4096 433 against
+// 432).
+// The smallest tiles are taken while they leave no CU with more than one (us per
+// step with walls, 8x8 / 8x16 / 16x16: FP64 128x128 4.4 / 4.9 / 5.7, 256x128 5.8 / 5.2 /
+// 5.9, 256x256 8.0 / 7.3 / 6.6; FP32 4.6 / 5.0 / 5.1, 5.5 / 5.1 / 5.3, 7.7 / 6.6 / 5.6).
 // FP32 with FP64 sums, whose collisions bound it, takes 16 x 16 tiles only where
 // their rings' columns, 6 to a tile, are less than half of the lattice's (0.6 of
 // them up to four tiles per CU, any share up to the two that run at once).  us
